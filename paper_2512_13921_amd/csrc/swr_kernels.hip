@@ -857,38 +857,69 @@ __global__ __launch_bounds__(TW * 64, 2) void swr_bwd_agg_kernel(Params p) {
 
 // Stage II of the exact recurrence: the carrier recurrence over the runs of
 // one sequence (Alg. "Hierarchical Block Parallel Inference", global carrier
-// solve, here at run granularity), one thread per (sequence, channel).  The
-// runs' aggregates are loaded eight at a time ahead of the dependent chain.
-__global__ __launch_bounds__(256) void swr_scan_kernel(ScanParams q) {
-    const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (idx >= q.seqs * q.D) return;
-    const int64_t seq = idx / q.D, ch = idx - seq * q.D;
-    const float* v = q.agg_v + seq * q.nruns * q.D + ch;
-    const float* pp = q.p_per_channel ? q.agg_p + seq * q.nruns * q.D + ch : q.agg_p + seq * q.nruns;
-    const int64_t pstride = q.p_per_channel ? q.D : 1;
-    float* cy = q.carry + seq * q.nruns * q.D + ch;
-    float S = q.init ? q.init[idx] : 0.0f;
-    constexpr int G = 8;
-    for (int64_t r0 = 0; r0 < q.nruns; r0 += G) {
-        float vv[G], pv[G];
+// solve, here at run granularity).
+//
+// Latency bounds it: a chain over the sequence's runs, a few MB at most.  So
+// the chain is cut: a workgroup owns 16 channels of one sequence and SEGS
+// segments of its runs, each thread folds one segment's aggregates into
+// (product, state), the segments' results meet in LDS, and every thread walks
+// its segment again from the state entering it (from registers where the
+// segment is one batch of loads, else read again, from L2).  One thread per
+// channel over all runs, eight loads ahead, took 152 us for 1096 runs
+// (6 sequences of packed 64-channel heads), this 11; for 508 runs 74, 7.
+constexpr int kScanBatch = 8;      // aggregates a thread loads at a time
+constexpr int64_t kScanShort = 16 * kScanBatch;   // runs that 16 segments hold in registers
+
+template <int SEGS>
+__global__ __launch_bounds__(SEGS * 16) void swr_scan_kernel(ScanParams q) {
+    __shared__ float s_P[SEGS][16], s_V[SEGS][16];
+    const int c = threadIdx.x & 15, sg = threadIdx.x >> 4;
+    const int64_t per = q.D / 16, units = q.seqs * per;   // 16-channel units
+    for (int64_t unit = blockIdx.x; unit < units; unit += gridDim.x) {
+        const int64_t seq = unit / per, ch = unit % per * 16 + c;
+        const float* v = q.agg_v + seq * q.nruns * q.D + ch;
+        const float* pp = q.p_per_channel ? q.agg_p + seq * q.nruns * q.D + ch : q.agg_p + seq * q.nruns;
+        const int64_t pstride = q.p_per_channel ? q.D : 1;
+        float* cy = q.carry + seq * q.nruns * q.D + ch;
+        const int64_t len = (q.nruns + SEGS - 1) / SEGS;
+        const int64_t lo = min(sg * len, q.nruns), hi = min(lo + len, q.nruns);   // in chain order
+        float vv[kScanBatch], pv[kScanBatch];
+        auto load = [&](int64_t j0) {   // aggregates j0 ... of this segment, in chain order
 #pragma unroll
-        for (int g = 0; g < G; ++g) {
-            const int64_t j = r0 + g;
-            const int64_t r = q.reverse ? q.nruns - 1 - j : j;
-            vv[g] = j < q.nruns ? v[r * q.D] : 0.0f;
-            pv[g] = j < q.nruns ? pp[r * pstride] : 1.0f;
-        }
+            for (int g = 0; g < kScanBatch; ++g) {
+                const int64_t j = j0 + g, r = q.reverse ? q.nruns - 1 - j : j;
+                vv[g] = j < hi ? v[r * q.D] : 0.0f;
+                pv[g] = j < hi ? pp[r * pstride] : 1.0f;
+            }
+        };
+        float P = 1.0f, V = 0.0f;
+        for (int64_t j0 = lo; j0 < hi; j0 += kScanBatch) {
+            load(j0);
 #pragma unroll
-        for (int g = 0; g < G; ++g) {
-            const int64_t j = r0 + g;
-            if (j < q.nruns) {
-                const int64_t r = q.reverse ? q.nruns - 1 - j : j;
-                cy[r * q.D] = S;
-                S = pv[g] * S + vv[g];
+            for (int g = 0; g < kScanBatch; ++g) {
+                V = __builtin_fmaf(pv[g], V, vv[g]);
+                P *= pv[g];
             }
         }
+        s_P[sg][c] = P;
+        s_V[sg][c] = V;
+        __syncthreads();
+        float S = q.init ? q.init[seq * q.D + ch] : 0.0f;
+        for (int s = 0; s < sg; ++s) S = __builtin_fmaf(s_P[s][c], S, s_V[s][c]);
+        for (int64_t j0 = lo; j0 < hi; j0 += kScanBatch) {
+            if (len > kScanBatch) load(j0);
+#pragma unroll
+            for (int g = 0; g < kScanBatch; ++g) {
+                const int64_t j = j0 + g;
+                if (j < hi) {
+                    cy[(q.reverse ? q.nruns - 1 - j : j) * q.D] = S;
+                    S = __builtin_fmaf(pv[g], S, vv[g]);
+                }
+            }
+        }
+        if (q.fin && sg == SEGS - 1) q.fin[seq * q.D + ch] = S;
+        __syncthreads();   // every read of the segments' results precedes the next unit's
     }
-    if (q.fin) q.fin[idx] = S;
 }
 
 // ---------------------------------------------------------------------------
@@ -1068,8 +1099,8 @@ __global__ __launch_bounds__(256) void swr_step_kernel(StepParams q) {
 // decays are loaded at once, one token a lane (a decay per head) or eight
 // rows a lane group at a time (a decay per channel), and multiplied by
 // doubling over the lanes, instead of one dependent load and product per
-// token (forward and state of a
-// 131072-token prompt, H32 D64: 420.6 -> 396.8 us).
+// token (forward and state of a 131072-token prompt, H32 D64: 420.6 ->
+// 396.8 us).
 template <class IO, int CPL, bool PC, bool FEAT>
 __global__ __launch_bounds__(256) void swr_state_kernel(StateParams q) {
     constexpr int D = CPL * SB;
@@ -2038,10 +2069,16 @@ hipError_t launch_gate_reduce(const Params& p, int dtype, int D, void* stream) {
     return dtype == 1 ? launch_gate_reduce_io<IoBf16>(p, D, st) : launch_gate_reduce_io<IoF32>(p, D, st);
 }
 
+// (16 segments where each is one batch of loads, which few threads then hold;
+// 64 beyond that, whose shorter segments weigh more than their threads.)
 hipError_t launch_scan(const ScanParams& q, void* stream) {
-    const int64_t n = q.seqs * q.D;
+    const int64_t n = q.seqs * (q.D / 16);
     if (n == 0) return hipSuccess;
-    hipLaunchKernelGGL(swr_scan_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, (hipStream_t)stream, q);
+    const dim3 grid((unsigned)std::min<int64_t>(n, 1 << 20));
+    if (q.nruns <= kScanShort)
+        hipLaunchKernelGGL((swr_scan_kernel<16>), grid, dim3(256), 0, (hipStream_t)stream, q);
+    else
+        hipLaunchKernelGGL((swr_scan_kernel<64>), grid, dim3(1024), 0, (hipStream_t)stream, q);
     return hipGetLastError();
 }
 
