@@ -201,7 +201,11 @@ int swr_abi_version(void);
  * composing the published aggregates of the chunks before it (a look-back
  * between workgroups in a fixed pattern, so that repeated calls give the same
  * bits): it reads every input once.  The backward does the same, from each
- * sequence's end, for heads of up to 64 channels (one decay per head).  A
+ * sequence's end, for heads of up to 64 channels (one decay per head).  With
+ * one decay per head, problems of few bytes or few sequences, where that chain
+ * and not the bytes would set the time, keep the three stages, and sequences
+ * of up to 128 tokens run as a single run in either direction (the choice
+ * depends on the problem's sizes alone).  A
  * chunk waits only for chunks that are already running, and gives up after
  * 65536 polls (never expected): it then adds one to the workspace's second
  * 32-bit integer and continues from NaN, so that every output depending on
@@ -221,7 +225,8 @@ int swr_abi_version(void);
  * NULL when that size is 0).  Its contents are scratch and are overwritten;
  * two calls in flight at once need two workspaces.  After a one-pass call's
  * work has completed, its second 32-bit integer holds the number of waits
- * that gave up (see above; 0 in every correct run).
+ * that gave up (see above; 0 in every correct run); it holds 0 after a call
+ * that kept the three stages for its sizes, too.
  * ------------------------------------------------------------------------ */
 
 /* Bytes of workspace swr_exact_forward / swr_exact_backward need for this

@@ -424,9 +424,13 @@ int64_t bwd_agg_len(const swr_problem_t* p, const Resolved& r) {
 // Workspace of the exact recurrence, in float32 elements: per (batch, head)
 // and aggregate run, the run's aggregate end state (D), the value entering
 // the run (D) and the run's decay product (1, or D for a per-channel decay),
-// for the largest of the launches' run counts.
+// for the largest of the launches' run counts.  Where the one-pass chain is
+// the other route (one decay per head, heads not packed) the arrays start
+// past its two counters, so that the count of waits that gave up reads zero
+// whichever route a call took.
 struct ExactWs {
     int64_t nr;       // runs per sequence the workspace is laid out for
+    int64_t head;     // float32 elements before the arrays
     int64_t floats;   // total float32 elements
 };
 
@@ -434,8 +438,9 @@ ExactWs exact_ws(const swr_problem_t* p, const Resolved& r) {
     ExactWs w;
     const int64_t na = r.empty ? 0 : (p->T + bwd_agg_len(p, r) - 1) / bwd_agg_len(p, r);
     w.nr = std::max(std::max(r.nruns, r.nruns_f), na);
+    w.head = !r.empty && !r.pc && r.pack == 1 ? 16 : 0;
     // a per-channel decay has one run decay product per channel
-    w.floats = p->B * p->H * w.nr * (2 * p->D + (r.pc || r.pack > 1 ? p->D : 1));
+    w.floats = w.head + p->B * p->H * w.nr * (2 * p->D + (r.pc || r.pack > 1 ? p->D : 1));
     return w;
 }
 
@@ -512,6 +517,39 @@ bool use_chain_bwd(const swr_problem_t* p, const Resolved& r) {
     return !cw.pcp && cw.hs == 0 && cw.cpl <= 4;
 }
 
+// Whether a call takes the three stages although it could chain chunks (one
+// decay per head).  The chain reads every input once, but a sequence's chunks
+// wait for one another, about 0.14 us a chunk, and its flags are reset first;
+// the stages read x, b and a (backward: c, dy and a) twice and have no chain.
+// So the stages win where the bytes are few: small problems, and few
+// sequences (`row`: the bytes of one token of all of them), whose bytes grow
+// no faster with the length than the chain does.  Measured, chain against
+// stages, bf16.  Forward: D 64, 4 sequences of 32768 54 / 29 us, 8 of 131072
+// 198 / 164, 16 of 8192 40 / 28, 16 of 32768 79 / 90, 64 of 2048 31 / 29, 128
+// of 2048 42 / 49; D 128, 2 of 131072 171 / 95, 4 of 131072 194 / 151, 8 of
+// 32768 78 / 78, 16 of 8192 44 / 48; float32 D 128 (whose chain runs halves of
+// 64), 4 of 2048 15 / 16, 4 of 8192 30 / 27.  Backward, D 64: 4 of 131072
+// 215 / 160, 8 of 8192 34 / 28, 8 of 32768 74 / 77, 16 of 131072 523 / 468, 32
+// of 131072 928 / 1047; chains of up to 32 chunks are within 10%.
+bool prefer_stages(const swr_problem_t* p, const Resolved& r, bool backward) {
+    const int64_t nch = (p->T + swr::chain_tokens() - 1) / swr::chain_tokens();
+    const int64_t row = p->B * p->H * p->D * r.es, total = row * p->T;
+    if (backward)
+        return nch > 32 && (total <= (int64_t)12 << 20 || row <= 512 || (row <= 2048 && nch >= 512));
+    if (r.es == 4 && nch < 64) return false;
+    return total <= (int64_t)24 << 20 || row <= 1024;
+}
+
+// Sequences of up to 128 tokens (one step of the backward's eight waves) run
+// as one run: no stage I or II, the sweep starts from h0 (dh_last) and stores
+// h_last (dh0) itself; one launch instead of two or three.  bf16, 15 sequences
+// of 128 tokens, D 64: forward 10.8 -> 7.5 us, backward 13.2 -> 10.4; of 256
+// tokens the backward's two steps would take 15.7 us against 14.6.
+constexpr int64_t kOneRunTokens = 128;
+bool one_run(const swr_problem_t* p, const Resolved& r) {
+    return !r.empty && p->run_len == 0 && p->T <= kOneRunTokens;
+}
+
 // The one-pass forward of bf16 heads of 64 channels taken two at a time
 // (16-byte lane slices): the per-channel layout over the pairs' 128 channels.
 int64_t chain_pair_floats(const swr_problem_t* p) {
@@ -535,9 +573,18 @@ int64_t exact_ws_floats(const swr_problem_t* p, const Resolved& r) {
     return f;
 }
 
+// The launch plan of one run over the whole sequence: steps of tw sub-blocks,
+// `groups` workgroups per batch entry.
+void set_one_run(const swr_problem_t* p, swr::Params* k, int tw, int64_t groups) {
+    const int64_t step = std::max<int64_t>(16 * tw, p->block);
+    k->run_len = (p->T + step - 1) / step * step;
+    k->nruns = 1;
+    k->nwork = p->B * groups;
+}
+
 // Pointers into the workspace for one launch.
 void exact_arrays(const swr_problem_t* p, const ExactWs& w, void* ws, float** v, float** carry, float** prod) {
-    float* f = (float*)ws;
+    float* f = (float*)ws + w.head;
     const int64_t n = p->B * p->H * w.nr * p->D;
     *v = f;
     *carry = f + n;
@@ -574,24 +621,32 @@ int swr::exact_forward_impl(const swr_problem_t* p, const void* x, const void* a
     int rc = resolve_for(p, &r, {x, b, c, (const void*)y});
     if (rc != SWR_OK) return rc;
     if (!r.natural) return SWR_ERR_UNSUPPORTED;
-    const ExactWs w = exact_ws(p, r);
+    ExactWs w = exact_ws(p, r);
     // the library's static array may hold the three stages' arrays but not the
     // one pass's: the allocation-free call then runs the three stages.  bf16
     // heads of 64 channels run in pairs where the pointers and strides allow.
 #ifndef SWR_EXACT_CHAIN_PAIR
 #define SWR_EXACT_CHAIN_PAIR 1
 #endif
+    if (scratch && w.floats * 4 > scratch_bytes) {   // (the counters are the chain's only)
+        w.floats -= w.head;
+        w.head = 0;
+    }
+    const bool stages_fit = !scratch || w.floats * 4 <= scratch_bytes;
     Resolved rp;
-    const bool pair = SWR_EXACT_CHAIN_PAIR && use_chain(p, r) && !r.pc && resolve_for(p, &rp, {x, b, c, (const void*)y}, true) == SWR_OK &&
-                      rp.pair && (!scratch || chain_pair_floats(p) * 4 <= scratch_bytes);
-    const bool chain = !pair && use_chain(p, r) && (!scratch || chain_ws(p, r).floats * 4 <= scratch_bytes);
+    bool pair = SWR_EXACT_CHAIN_PAIR && use_chain(p, r) && !r.pc && resolve_for(p, &rp, {x, b, c, (const void*)y}, true) == SWR_OK &&
+                rp.pair && (!scratch || chain_pair_floats(p) * 4 <= scratch_bytes);
+    bool chain = !pair && use_chain(p, r) && (!scratch || chain_ws(p, r).floats * 4 <= scratch_bytes);
+    const bool single = one_run(p, r);   // (needs no array, but is refused where nothing fits)
+    const bool fits = pair || chain || stages_fit;
+    if (single || (!r.pc && stages_fit && prefer_stages(p, r, false))) pair = chain = false;
     const int64_t wfloats = pair ? chain_pair_floats(p) : chain ? chain_ws(p, r).floats : w.floats;
     const int64_t seqs = p->B * p->H, sbytes = seqs * p->D * 4;
     if (seqs == 0) return SWR_OK;
     if (!r.empty && (!x || !a || !b || !c || !y)) return SWR_ERR_NULL;
     if (scratch) {
         // the library's own array: disjoint from every caller buffer, located later
-        if (wfloats * 4 > scratch_bytes) return SWR_ERR_SCRATCH;
+        if (!fits) return SWR_ERR_SCRATCH;
         workspace = nullptr;
     } else if (wfloats > 0 && !workspace) {
         return SWR_ERR_NULL;
@@ -673,6 +728,15 @@ int swr::exact_forward_impl(const swr_problem_t* p, const void* x, const void* a
     if (w.floats > 0) exact_arrays(p, w, workspace, &wv, &wc, &wp);
     swr::Params k = make_params(p, r, false);
     k.x = x; k.a = a; k.b = b; k.c = c;
+    if (use_chain(p, r) && (single || w.head)) k.chain_ctr = (int32_t*)workspace;
+    if (single) {   // stage III alone, from h0
+        set_one_run(p, &k, r.fwd.tw, r.hv / r.fwd.hw);
+        k.carry = h0; k.h_last = h_last;
+        k.agg_len = k.run_len; k.agg_nruns = 1;
+        k.y = y; k.carriers = carriers;
+        return swr::launch(k, p->dtype, r.dk, r.fwd, false, r.pc, r.pack, swr::kExact, stream) == hipSuccess
+                   ? SWR_OK : SWR_ERR_HIP;
+    }
     k.agg_v = wv; k.agg_p = wp; k.carry = wc;
     k.agg_len = k.run_len; k.agg_nruns = k.nruns;
     // Stage I: local solves of every run, keeping each run's end state and decay product.
@@ -729,7 +793,8 @@ int swr_exact_backward(const swr_problem_t* p, const void* x, const void* a, con
             if (overlap(outs[i], outs[j])) return SWR_ERR_ALIAS;
     }
 
-    if (use_chain_bwd(p, r)) {   // one pass: chunks from the sequences' ends, chained by a look-back
+    const bool single = one_run(p, r);
+    if (!single && use_chain_bwd(p, r) && !prefer_stages(p, r, true)) {   // one pass: chunks from the sequences' ends, chained by a look-back
         const ChainWs cw = chain_ws(p, r);
         float* f = (float*)workspace;
         swr::Params k = make_params(p, r, true);
@@ -750,6 +815,16 @@ int swr_exact_backward(const swr_problem_t* p, const void* x, const void* a, con
     if (w.floats > 0) exact_arrays(p, w, workspace, &wv, &wc, &wp);
     swr::Params k = make_params(p, r, true);
     k.x = x; k.a = a; k.b = b; k.c = c; k.dy = dy;
+    if (use_chain_bwd(p, r)) k.chain_ctr = (int32_t*)workspace;
+    if (single) {   // stage III alone, from dh_last
+        set_one_run(p, &k, r.bwd.tw, r.hv / r.bwd.hw);
+        k.carry = dh_last; k.dh0 = dh0; k.h0 = h0;
+        k.agg_len = k.run_len; k.agg_nruns = 1;
+        k.dx = dx; k.da = da; k.db = db; k.dc = dc;
+        k.carriers = const_cast<float*>(carriers);
+        return swr::launch(k, p->dtype, r.dk, r.bwd, true, r.pc, r.pack, swr::kExact, stream) == hipSuccess
+                   ? SWR_OK : SWR_ERR_HIP;
+    }
     k.agg_v = wv; k.agg_p = wp; k.carry = wc; k.h0 = h0;
     k.agg_len = r.empty ? 1 : bwd_agg_len(p, r);
     k.agg_nruns = r.empty ? 0 : (p->T + k.agg_len - 1) / k.agg_len;

@@ -53,6 +53,12 @@
 namespace swr {
 namespace {
 
+// The exact calls that do not chain chunks leave the workspace's count of
+// look-back waits that gave up at zero too (p.chain_ctr: its start, or NULL).
+__device__ inline void clear_time_outs(const Params& p) {
+    if (p.chain_ctr && blockIdx.x == 0 && threadIdx.x == 0) p.chain_ctr[1] = 0;
+}
+
 // ---------------------------------------------------------------------------
 // Forward
 // ---------------------------------------------------------------------------
@@ -151,9 +157,10 @@ __global__ __launch_bounds__(TW * HW * 64, 3) void swr_fwd_kernel(Params p) {
     if constexpr (MODE == kExact) {   // the exact state entering the run (stage II's result)
         Row<IoF32, CPL> ci;
         const int64_t j = (wk.b * p.H + wk.h) * p.agg_nruns + wk.t_begin / p.agg_len;
-        ci.load(rsrc(p.carry + j * D), (uint32_t)(n * CPL) * 4u);
+        ci.load(rsrc(p.carry + j * D), in_range(p.carry != nullptr, (uint32_t)(n * CPL) * 4u));
 #pragma unroll
         for (int m = 0; m < CPL; ++m) e[m] = ci.get(m);
+        clear_time_outs(p);
     }
     float prod = 1.0f;   // kAggregate: decay product of the run so far
 
@@ -327,6 +334,11 @@ __global__ __launch_bounds__(TW * HW * 64, 3) void swr_fwd_kernel(Params p) {
             store_row<IO, CPL, kFwdStore>(ry, in_range(t >= wk.t_begin && t < wk.t_end, loff + (uint32_t)(r * rs)), yv);
         }
     }
+    if constexpr (MODE == kExact) {   // a single run's end state is the sequence's
+        if (p.h_last)
+            store_row<IoF32, CPL>(rsrc(p.h_last + (wk.b * p.H + wk.h) * D),
+                                  in_range(tw == 0 && grp == 0, (uint32_t)(n * CPL) * 4u), e);
+    }
     if constexpr (MODE == kAggregate) {   // the run's end state from zero, and its decay product
         store_row<IoF32, CPL>(rsrc(p.agg_v + slot * D), in_range(tw == 0 && grp == 0, (uint32_t)(n * CPL) * 4u), e);
         __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(int, prod), rsrc(p.agg_p + slot),
@@ -450,9 +462,10 @@ __global__ __launch_bounds__(TW * HW * 64, 2) void swr_bwd_kernel(Params p) {
     if constexpr (MODE == kExact) {   // the exact adjoint entering the run's end (stage II)
         Row<IoF32, CPL> ci;
         const int64_t j = seq * p.agg_nruns + (wk.t_end - 1) / p.agg_len;   // the run's last aggregate
-        ci.load(rsrc(p.carry + j * D), (uint32_t)(n * CPL) * 4u);
+        ci.load(rsrc(p.carry + j * D), in_range(p.carry != nullptr, (uint32_t)(n * CPL) * 4u));
 #pragma unroll
         for (int m = 0; m < CPL; ++m) eps[m] = ci.get(m);
+        clear_time_outs(p);
     }
     int buf = 0;
 
@@ -777,6 +790,10 @@ __global__ __launch_bounds__(TW * HW * 64, 2) void swr_bwd_kernel(Params p) {
             store_da(r, tot);
         }
     }
+    if constexpr (MODE == kExact) {   // what leaves a single run's first token leaves the sequence
+        if (p.dh0)
+            store_row<IoF32, CPL>(rsrc(p.dh0 + seq * D), in_range(tw == 0 && grp == 0, (uint32_t)(n * CPL) * 4u), eps);
+    }
 }
 
 // Stage I of the exact recurrence's backward: for every run, the adjoint that
@@ -905,7 +922,8 @@ __global__ __launch_bounds__(SEGS * 16) void swr_scan_kernel(ScanParams q) {
         s_V[sg][c] = V;
         __syncthreads();
         float S = q.init ? q.init[seq * q.D + ch] : 0.0f;
-        for (int s = 0; s < sg; ++s) S = __builtin_fmaf(s_P[s][c], S, s_V[s][c]);
+        const int last = q.nruns > 0 ? (int)((q.nruns - 1) / len) : 0;   // the last segment with runs
+        for (int s = 0; s < min(sg, last); ++s) S = __builtin_fmaf(s_P[s][c], S, s_V[s][c]);
         for (int64_t j0 = lo; j0 < hi; j0 += kScanBatch) {
             if (len > kScanBatch) load(j0);
 #pragma unroll
@@ -917,7 +935,7 @@ __global__ __launch_bounds__(SEGS * 16) void swr_scan_kernel(ScanParams q) {
                 }
             }
         }
-        if (q.fin && sg == SEGS - 1) q.fin[seq * q.D + ch] = S;
+        if (q.fin && sg == last) q.fin[seq * q.D + ch] = S;
         __syncthreads();   // every read of the segments' results precedes the next unit's
     }
 }
@@ -1274,9 +1292,11 @@ __global__ __launch_bounds__(TW * HW * 64, 3) void swr_fwd_pc_kernel(Params p) {
     for (int m = 0; m < CPL; ++m) { e[m] = 0.f; s[m] = 0.f; prod[m] = 1.f; }
     if constexpr (MODE == kExact) {
         Row<IoF32, CPL> ci;
-        ci.load(rsrc(p.carry + hb * p.agg_nruns * geo.Dr), geo.off(p.agg_nruns, wk.t_begin / p.agg_len) * 4u);
+        ci.load(rsrc(p.carry + hb * p.agg_nruns * geo.Dr),
+                in_range(p.carry != nullptr, geo.off(p.agg_nruns, wk.t_begin / p.agg_len) * 4u));
 #pragma unroll
         for (int m = 0; m < CPL; ++m) e[m] = ci.get(m);
+        clear_time_outs(p);
     }
     const int64_t t_stop = ((wk.t_end + l - 1) >> p.lshift) << p.lshift;
     const int64_t t_first = wk.t_begin - halo * STEP;
@@ -1368,6 +1388,10 @@ __global__ __launch_bounds__(TW * HW * 64, 3) void swr_fwd_pc_kernel(Params p) {
             store_row<IO, CPL, kFwdStore>(ry, in_range(t >= wk.t_begin && t < wk.t_end, loff + (uint32_t)(r * rs)), yv);
         }
     }
+    if constexpr (MODE == kExact) {   // a single run's end state is the sequence's
+        if (p.h_last)
+            store_row<IoF32, CPL>(rsrc(p.h_last + hb * geo.Dr), in_range(tw == 0 && grp == 0, geo.off(1, 0) * 4u), e);
+    }
     if constexpr (MODE == kAggregate) {   // the run's end state from zero and decay products
         const uint32_t o = in_range(tw == 0 && grp == 0, geo.off(p.nruns, wk.run) * 4u);
         store_row<IoF32, CPL>(rsrc(p.agg_v + hb * p.nruns * geo.Dr), o, e);
@@ -1437,9 +1461,11 @@ __global__ __launch_bounds__(TW * HW * 64, 2) void swr_bwd_pc_kernel(Params p) {
     if constexpr (MODE == kExact) {   // the exact adjoint entering the run's end (stage II)
         Row<IoF32, CPL> ci;
         // the run's last aggregate
-        ci.load(rsrc(p.carry + hb * p.agg_nruns * geo.Dr), geo.off(p.agg_nruns, (wk.t_end - 1) / p.agg_len) * 4u);
+        ci.load(rsrc(p.carry + hb * p.agg_nruns * geo.Dr),
+                in_range(p.carry != nullptr, geo.off(p.agg_nruns, (wk.t_end - 1) / p.agg_len) * 4u));
 #pragma unroll
         for (int m = 0; m < CPL; ++m) eps[m] = ci.get(m);
+        clear_time_outs(p);
     }
     int buf = 0;
 
@@ -1744,6 +1770,10 @@ __global__ __launch_bounds__(TW * HW * 64, 2) void swr_bwd_pc_kernel(Params p) {
                 store_row<IoF32, CPL, kBwdStore>(rda, in_range(t < wk.t_end, daoff + (uint32_t)(r * das)), vda);
             }
         }
+    }
+    if constexpr (MODE == kExact) {   // what leaves a single run's first token leaves the sequence
+        if (p.dh0)
+            store_row<IoF32, CPL>(rsrc(p.dh0 + hb * geo.Dr), in_range(tw == 0 && grp == 0, geo.off(1, 0) * 4u), eps);
     }
 }
 
