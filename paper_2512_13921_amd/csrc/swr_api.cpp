@@ -19,15 +19,9 @@ constexpr int64_t kMaxWorkgroups = 0x7fffffffLL;
 // sum in either order) or four of 64 (per-channel decay).
 constexpr int64_t kMaxD = 256;
 constexpr int64_t kMaxExtent = (int64_t)1 << 62;
-// Default grid sizes, measured on the MI355X (256 compute units) over the
-// benchmark workloads: the forward runs best with two 4-wave workgroups per
-// CU; the backward with one 8-wave workgroup per CU, and with more, shorter
-// runs when its workgroups are 4 waves (the lighter they are, the more).
-// Longer runs mean fewer halo re-reads.
+// Default grid size of the forward, measured on the MI355X (256 compute units)
+// over the benchmark workloads: two 4-wave workgroups per CU.
 int64_t fwd_workgroups(const swr::Shape& s) { return s.tw * s.hw == 4 ? 512 : 256; }
-int64_t bwd_workgroups(const swr::Shape& s, int cpl) {
-    return s.tw * s.hw == 8 ? 256 : (cpl == 8 ? 1024 : 8192);
-}
 
 // Run length (tokens, a multiple of step) that splits each sequence into
 // enough runs to give about `target` workgroups.
@@ -37,6 +31,52 @@ int64_t pick_run_len(int64_t T, int64_t seqs, int64_t step, int64_t target) {
     const int64_t runs = std::max<int64_t>(1, std::min(nsteps, want));
     return ((nsteps + runs - 1) / runs) * step;
 }
+
+// Run length of a sweep whose workgroups are resident `cap` at a time (the
+// compute units times the workgroups that fit one) and start with a halo of
+// `halo` tokens, which costs about half a step's work per token (the
+// backward's reads c, dy and a and stores nothing).  A few rounds of workgroups
+// cost
+//     ceil(workgroups / cap) * (run + halo / 2)
+// after another, of which the run length with the least is taken: a grid just
+// over a round would cost a whole one more (the uniform backward of 4 x 7 heads
+// of 64, T 61554: 268 workgroups where 256 fit, 802 us; 252, 477 us).  Where
+// runs of `len` tokens (0: never) make two rounds or more, they are taken:
+// short runs then even out the workgroups' ends.
+struct Sweep {
+    int64_t cap, len;
+};
+int64_t plan_run_len(int64_t T, int64_t units, int64_t step, int64_t halo, const Sweep& s) {
+    const int64_t nsteps = (T + step - 1) / step;
+    if (s.len > 0 && units * T / s.len >= 2 * s.cap) {   // whole rounds here too
+        const int64_t r = std::max<int64_t>(1, std::min(nsteps, units * T / s.len / s.cap * s.cap / units));
+        return (nsteps + r - 1) / r * step;
+    }
+    int64_t best = nsteps, cost = -1;
+    const int64_t first = (units + s.cap - 1) / s.cap;   // rounds of one run a sequence
+    for (int64_t k = first; k < first + 4; ++k) {         // the most runs that fit k rounds
+        const int64_t r = std::min(nsteps, k * s.cap / units);
+        const int64_t steps = (nsteps + r - 1) / r, runs = (nsteps + steps - 1) / steps;
+        const int64_t c = (units * runs + s.cap - 1) / s.cap * (2 * steps * step + (runs > 1 ? halo : 0));
+        if (cost < 0 || c <= cost) { best = steps; cost = c; }
+    }
+    return best * step;
+}
+
+// The backward's sweeps.  8 waves (l = 128): one workgroup a compute unit (165
+// to 254 VGPRs), two of lanes of 1 or 2 channels (82 to 127; recomputing its
+// carriers 2 channels a lane take up to 142); one round, since the runs' ends
+// cost less than further halos.  4 waves: two (three of packed heads, 165 VGPRs,
+// and of float32 heads of 64, 150), or four of the narrow ones, and
+// runs of 256 tokens once those make several rounds (512 for heads of 128 and
+// bf16 heads of 64, 128 where a token moves the most bytes: float32 with a
+// decay per channel), or twice that for bf16 heads of 64 or more without saved
+// carriers, whose halo is a step longer.  Against fixed grids of 256, 1024 (128
+// channels) and 8192 workgroups, bf16, saved carriers: D 64, l 64, 16 heads of
+// 16384 tokens 68.2 -> 48 us, of 65536 235 -> 211; a decay per channel, D 128,
+// l 64, 16 of 8192 95 -> 74; D 48, l 128, 48 of 24448 438 -> 299.
+struct Resolved;
+Sweep bwd_sweep(const Resolved& r, bool recompute);
 
 struct Dim {
     int64_t size, stride;
@@ -93,6 +133,31 @@ struct Resolved {
     int64_t nblocks;    // blocks per sequence
     int64_t carriers;   // float32 carriers of the whole problem
 };
+
+Sweep bwd_sweep(const Resolved& r, bool recompute) {
+    if (r.bwd.tw * r.bwd.hw == 8) return {r.cpl >= 4 || (r.cpl == 2 && recompute) ? 256 : 512, 0};
+    if (r.cpl <= 2) return {1024, 256};
+    if (r.pack > 1) return {recompute ? 512 : 768, 256};
+    const int64_t len = r.cpl == 8 || (r.es == 2 && !r.pc) ? 512 : r.pc && r.es == 4 ? 128 : 256;
+    // (a decay per channel: heads in four parts, or that leave lanes idle, ran
+    // as fast or faster with twice the workgroups)
+    const int64_t cap = r.pc && (r.hshift == 2 || r.nlane < 16) ? 1024 : r.cpl == 4 && r.es == 4 && !r.pc ? 768 : 512;
+    return {cap, recompute && r.es == 2 && !r.pc ? 2 * len : len};
+}
+
+// The backward's launch plan (recompute: without saved carriers).
+void plan_backward(const swr_problem_t* p, Resolved* r, bool recompute) {
+    const int64_t groups = p->B * r->hv / r->bwd.hw;   // work items per run position
+    if (p->run_len > 0)
+        r->run_len = p->run_len;
+    else if (r->empty)
+        r->run_len = r->step;
+    else
+        r->run_len = plan_run_len(p->T, groups, r->step, p->block,
+                                  bwd_sweep(*r, recompute));
+    r->nruns = r->empty ? 0 : (p->T + r->run_len - 1) / r->run_len;
+    r->nwork = groups * r->nruns;
+}
 
 int resolve(const swr_problem_t* p, Resolved* r, bool allow_pack = true, bool allow_pair = false) {
     if (!p) return SWR_ERR_NULL;
@@ -173,19 +238,16 @@ int resolve(const swr_problem_t* p, Resolved* r, bool allow_pack = true, bool al
         if (g * ((p->T + rl - 1) / rl) < fwd_workgroups(r->fwd)) r->fwd = swr::fwd_shape_single();
     }
     const int64_t groups = seqs / r->fwd.hw;       // forward work items per run position
-    const int64_t groups_b = seqs / r->bwd.hw;     // backward work items per run position
+    plan_backward(p, r, false);
     if (p->run_len > 0) {
-        r->run_len = r->run_len_f = p->run_len;
+        r->run_len_f = p->run_len;
     } else if (r->empty) {
-        r->run_len = r->run_len_f = r->step;
+        r->run_len_f = r->step;
     } else {
-        r->run_len = pick_run_len(p->T, groups_b, r->step, bwd_workgroups(r->bwd, r->cpl));
         r->run_len_f = pick_run_len(p->T, groups, r->step, fwd_workgroups(r->fwd));
     }
-    r->nruns = r->empty ? 0 : (p->T + r->run_len - 1) / r->run_len;
     r->nruns_f = r->empty ? 0 : (p->T + r->run_len_f - 1) / r->run_len_f;
     if (!r->empty && std::max(r->nruns, r->nruns_f) > kMaxWorkgroups / seqs) return SWR_ERR_UNSUPPORTED;
-    r->nwork = groups_b * r->nruns;
     r->nwork_f = groups * r->nruns_f;
     r->nblocks = (p->T + p->block - 1) / p->block;
     r->carriers = p->B * p->H * r->nblocks * p->D;
@@ -393,6 +455,7 @@ int swr_backward(const swr_problem_t* p, const void* x, const void* a, const voi
             if (overlap(outs[i], outs[j])) return SWR_ERR_ALIAS;
     }
 
+    if (!carriers) plan_backward(p, &r, true);
     swr::Params k = make_params(p, r, true);
     k.x = x; k.a = a; k.b = b; k.c = c; k.dy = dy;
     k.dx = dx; k.da = da; k.db = db; k.dc = dc;
@@ -988,18 +1051,16 @@ int uni_resolve(const swr_problem_t* p, UniPlan* u, bool backward) {
         u->nruns = u->nwork = 0;
         return SWR_OK;
     }
-    // The backward: one 8-wave workgroup per compute unit.  The forward: runs
-    // between those of about 2048 and about 512 workgroups, as close to 2048
-    // tokens as that allows (measured on MI355X against 512 workgroups:
-    // B8 T16384 H16 d128 455 -> 438 us, B1 T131072 H32 d64 466 -> 449, B16
-    // T8192 H32 d64 426 -> 423).
+    // The backward: one 8-wave workgroup per compute unit (two of heads of 16
+    // channels: 117 VGPRs against 156 and 236), one round.  The forward: two,
+    // and runs of 2048 tokens once those make several rounds (measured on
+    // MI355X against 512 workgroups: B8 T16384 H16 d128 455 -> 438 us, B1
+    // T131072 H32 d64 466 -> 449, B16 T8192 H32 d64 426 -> 423).
     if (p->run_len > 0)
         u->run_len = p->run_len;
-    else if (backward)
-        u->run_len = pick_run_len(p->T, groups, p->block, 256);
     else
-        u->run_len = std::max(pick_run_len(p->T, groups, p->block, 2048),
-                              std::min<int64_t>(2048, pick_run_len(p->T, groups, p->block, 512)));
+        u->run_len = plan_run_len(p->T, groups, p->block, p->block,
+                                  backward ? Sweep{u->cpl == 1 ? 512 : 256, 0} : Sweep{512, 2048});
     u->nruns = (p->T + u->run_len - 1) / u->run_len;
     if (u->nruns > kMaxWorkgroups / groups) return SWR_ERR_UNSUPPORTED;
     u->nwork = groups * u->nruns;
@@ -1202,11 +1263,18 @@ int swr_backward_shared_gates(const swr_problem_t* p, int64_t group, const int64
         k.Hv = (p->H / group) << k.hshift;
         const int64_t units = p->B * k.Hv;
         const int tw = p->block >= 128 ? 8 : 4;
-        k.run_len = p->run_len > 0 ? p->run_len : pick_run_len(p->T, units, 16 * tw, 256);
+        const int cpl = (int)(std::min<int64_t>(p->D, 64) / 16);
+        // 8 waves: one workgroup a compute unit, two of 16-channel heads (123
+        // VGPRs); 4 waves two to four (253, 159, 123 VGPRs).  Against 256
+        // workgroups: 16 x 8 groups of 4 heads of 64, T 8192, l 64 757 -> 525
+        // us; 4 x 4 of 8 heads of 32, T 13312 236 -> 191; 4 x 6 of 2 of 16,
+        // T 32640, float32 245 -> 149.
+        const Sweep sweep{tw == 8 ? (cpl == 1 ? 512 : 256) : cpl == 4 || (cpl == 2 && r.es == 4) ? 512
+                          : cpl == 2 ? 768 : 1024, 0};
+        k.run_len = p->run_len > 0 ? p->run_len : plan_run_len(p->T, units, 16 * tw, p->block, sweep);
         k.nruns = (p->T + k.run_len - 1) / k.run_len;
         if (k.nruns > kMaxWorkgroups / units) return SWR_ERR_UNSUPPORTED;
         k.nwork = units * k.nruns;
-        const int cpl = (int)(std::min<int64_t>(p->D, 64) / 16);
         return swr::launch_grouped_backward(k, p->dtype, cpl, tw, stream) == hipSuccess ? SWR_OK : SWR_ERR_HIP;
     }
     k.gws = (float*)workspace;
