@@ -3,7 +3,10 @@
 The functions below mirror the C ABI in ``include/swr.h`` (same names, same
 arguments) and only marshal torch tensors into pointers, strides and the
 current HIP stream; every step of the computation runs in the library's HIP
-kernels.  There is no CPU fallback: without the built library, or without a
+kernels.  The ordinary call (plain GPU tensors that pass every check, outputs
+allocated here) is marshalled in native code (``csrc/swr_binding.cpp``); the
+Python code below takes the others and raises what there is to raise.  There
+is no CPU fallback: without the built library, or without a
 GPU, the calls raise.
 
 Layouts: ``x, b, c, y, dy, dx, db, dc`` are ``[B, T, H, D]`` (channels
@@ -121,6 +124,43 @@ def load():
             raise RuntimeError("libswr.so ABI version does not match the binding")
         _lib = lib
     return _lib
+
+
+# The C ABI's entry points that the native marshalling calls, in its order.
+_BOUND = ("swr_forward", "swr_backward", "swr_exact_workspace_bytes", "swr_exact_forward", "swr_exact_backward",
+          "swr_step", "swr_exact_step", "swr_decode_state", "swr_uniform_forward", "swr_uniform_backward",
+          "swr_forward_shared_gates", "swr_backward_shared_gates", "swr_shared_gates_workspace_bytes")
+_native = None   # (the library it is bound to, the extension module)
+
+
+def _fast():
+    """The native marshalling, bound to the loaded library."""
+    global _native
+    lib = _lib or load()
+    if _native is None or _native[0] is not lib:
+        if not os.path.exists(_build.BINDING):
+            _build.build_binding()
+        _torch()
+        from . import _binding
+        _binding.bind(*(ctypes.cast(getattr(lib, n), ctypes.c_void_p).value for n in _BOUND))
+        _native = (lib, _binding)
+    return _native[1]
+
+
+def _flags(residual, sigmoid_decay, sigmoid_pregate):
+    return ((SWR_FLAG_RESIDUAL if residual else 0) | (SWR_FLAG_SIGMOID_DECAY if sigmoid_decay else 0)
+            | (SWR_FLAG_SIGMOID_PREGATE if sigmoid_pregate else 0))
+
+
+def _raw(stream):
+    return None if stream is None else stream.cuda_stream
+
+
+def _checked(r, what):
+    """A native call's results; a status of the C ABI raises."""
+    if type(r) is int:
+        raise SwrError(r, what)
+    return r
 
 
 def swr_error_string(code: int) -> str:
@@ -257,6 +297,11 @@ def swr_forward(x, a, b, c, block, residual=False, y=None, carriers=None, save_c
 
     Returns y, or (y, carriers) when ``save_carriers`` is true or a carrier
     tensor is passed in (it is filled)."""
+    r = _fast().forward(x, a, b, c, block, _flags(residual, sigmoid_decay, sigmoid_pregate), run_len, y, carriers,
+                        bool(save_carriers) or carriers is not None, _raw(stream))
+    if r is not None:
+        y, v = _checked(r, "swr_forward")
+        return y if v is None else (y, v)
     torch = _torch()
     problem = _problem_from(x, a, block, residual, run_len, sigmoid_decay, sigmoid_pregate)
     _same_layout(x, b, c)
@@ -291,6 +336,11 @@ def swr_backward(x, a, b, c, dy, carriers, block, residual=False, outputs=None, 
     """(dx, da, db, dc) of the SWR forward given dy and the forward's block
     carriers (see ``include/swr.h``), or carriers=None: the kernel then
     recomputes each carrier from the previous block's x, b, a."""
+    if outputs is None:
+        r = _fast().backward(x, a, b, c, dy, carriers, block, _flags(residual, sigmoid_decay, sigmoid_pregate),
+                             run_len, _raw(stream))
+        if r is not None:
+            return _checked(r, "swr_backward")
     torch = _torch()
     problem = _problem_from(x, a, block, residual, run_len, sigmoid_decay, sigmoid_pregate)
     _same_layout(x, b, c, dy)
@@ -352,6 +402,12 @@ def _opt(t):
 
 def _exact_forward(noalloc, x, a, b, c, block, h0, residual, y, carriers, save_carriers, h_last,
                    want_h_last, workspace, run_len, stream, sigmoid_decay, sigmoid_pregate):
+    if not noalloc and y is None and carriers is None and h_last is None and workspace is None:
+        r = _fast().exact_forward(x, a, b, c, block, _flags(residual, sigmoid_decay, sigmoid_pregate), run_len, h0,
+                                  bool(save_carriers), bool(want_h_last), _raw(stream))
+        if r is not None:
+            out = tuple(t for t in _checked(r, "swr_exact_forward") if t is not None)
+            return out[0] if len(out) == 1 else out
     torch = _torch()
     problem = _problem_from(x, a, block, residual, run_len, sigmoid_decay, sigmoid_pregate)
     _same_layout(x, b, c)
@@ -411,6 +467,12 @@ def swr_exact_backward(x, a, b, c, dy, carriers, block, h0=None, dh_last=None, r
     """(dx, da, db, dc) of the exact recurrence, plus dh0 when ``want_dh0``;
     ``carriers`` are the exact forward's block carriers, ``dh_last`` the
     gradient flowing into its final state (or None)."""
+    if outputs is None and workspace is None:
+        r = _fast().exact_backward(x, a, b, c, dy, carriers, block, _flags(residual, sigmoid_decay, sigmoid_pregate),
+                                   run_len, h0, dh_last, bool(want_dh0), _raw(stream))
+        if r is not None:
+            r = _checked(r, "swr_exact_backward")
+            return r if want_dh0 else r[:4]
     torch = _torch()
     problem = _problem_from(x, a, block, residual, run_len, sigmoid_decay, sigmoid_pregate)
     _same_layout(x, b, c, dy)
@@ -457,6 +519,11 @@ def swr_step(x, a, b, c, block, t0, state=None, residual=False, y=None, stream=N
     """K = x.shape[1] tokens at sequence positions t0 .. t0+K-1 in recurrent
     form (see ``include/swr.h``).  ``state`` ([B, H, 2, D] float32; None =
     zeros, i.e. t0 = 0) is updated in place.  Returns (y, state)."""
+    if state is not None and type(t0) is int and t0 >= 0:
+        r = _fast().step(x, a, b, c, block, _flags(residual, sigmoid_decay, sigmoid_pregate), t0, state, y,
+                         _raw(stream))
+        if r is not None:
+            return _checked(r, "swr_step"), state
     torch = _torch()
     problem = _problem_from(x, a, block, residual, 0, sigmoid_decay, sigmoid_pregate)
     _same_layout(x, b, c)
@@ -476,6 +543,10 @@ def swr_exact_step(x, a, b, c, state=None, residual=False, y=None, stream=None,
                    sigmoid_decay=False, sigmoid_pregate=False):
     """K tokens of the exact recurrence from the state h ([B, H, D] float32,
     updated in place; None = zeros).  Returns (y, state)."""
+    if state is not None:   # (position -1: the exact recurrence)
+        r = _fast().step(x, a, b, c, 16, _flags(residual, sigmoid_decay, sigmoid_pregate), -1, state, y, _raw(stream))
+        if r is not None:
+            return _checked(r, "swr_exact_step"), state
     torch = _torch()
     problem = _problem_from(x, a, 16, residual, 0, sigmoid_decay, sigmoid_pregate)
     _same_layout(x, b, c)
@@ -494,6 +565,10 @@ def swr_exact_step(x, a, b, c, state=None, residual=False, y=None, stream=None,
 def swr_decode_state(x, a, carriers, block, state=None, stream=None, sigmoid_decay=False):
     """swr_step's state after a jagged-window forward over all of x's tokens,
     from that forward's block carriers (x gives the shape and strides only)."""
+    if state is None:
+        r = _fast().decode_state(x, a, carriers, block, _flags(False, sigmoid_decay, False), _raw(stream))
+        if r is not None:
+            return _checked(r, "swr_decode_state")
     torch = _torch()
     problem = _problem_from(x, a, block, False, 0, sigmoid_decay, False)
     carriers = _carrier_tensor(x, block, carriers)
@@ -540,6 +615,12 @@ def swr_forward_shared_gates(x, a, b, c, block, group, residual=False, y=None, c
     """Jagged-window forward where heads g*group .. g*group+group-1 share the
     gates b[:, :, g] and c[:, :, g] (b, c: [B, T, H / group, D]).  Returns y,
     or (y, carriers) as swr_forward."""
+    if y is None and carriers is None:
+        r = _fast().forward_shared_gates(x, a, b, c, block, _flags(residual, sigmoid_decay, sigmoid_pregate), run_len,
+                                         group, bool(save_carriers), _raw(stream))
+        if r is not None:
+            y, v = _checked(r, "swr_forward_shared_gates")
+            return y if v is None else (y, v)
     torch = _torch()
     problem = _problem_from(x, a, block, residual, run_len, sigmoid_decay, sigmoid_pregate)
     _gates_check(x, b, group)
@@ -562,6 +643,12 @@ def swr_backward_shared_gates(x, a, b, c, dy, carriers, block, group, residual=F
                               workspace=None, run_len=0, stream=None, sigmoid_decay=False,
                               sigmoid_pregate=False):
     """(dx, da, db, dc) of swr_forward_shared_gates; db and dc have b's layout."""
+    if outputs is None and workspace is None:
+        r = _fast().backward_shared_gates(x, a, b, c, dy, carriers, block,
+                                          _flags(residual, sigmoid_decay, sigmoid_pregate), run_len, group,
+                                          _raw(stream))
+        if r is not None:
+            return _checked(r, "swr_backward_shared_gates")
     torch = _torch()
     problem = _problem_from(x, a, block, residual, run_len, sigmoid_decay, sigmoid_pregate)
     _gates_check(x, b, group)
@@ -609,6 +696,11 @@ def swr_uniform_forward(x, a, b, c, window, residual=False, y=None, run_len=0, s
                         sigmoid_decay=False, sigmoid_pregate=False):
     """y of the uniform-window recurrence (every token sees its ``window``
     most recent tokens; see ``include/swr.h``)."""
+    if y is None:
+        r = _fast().uniform_forward(x, a, b, c, window, _flags(residual, sigmoid_decay, sigmoid_pregate), run_len,
+                                    _raw(stream))
+        if r is not None:
+            return _checked(r, "swr_uniform_forward")
     torch = _torch()
     problem = _problem_from(x, a, window, residual, run_len, sigmoid_decay, sigmoid_pregate)
     _same_layout(x, b, c)
@@ -626,6 +718,11 @@ def swr_uniform_forward(x, a, b, c, window, residual=False, y=None, run_len=0, s
 def swr_uniform_backward(x, a, b, c, dy, window, residual=False, outputs=None, run_len=0, stream=None,
                          sigmoid_decay=False, sigmoid_pregate=False):
     """(dx, da, db, dc) of the uniform-window forward given dy."""
+    if outputs is None:
+        r = _fast().uniform_backward(x, a, b, c, dy, window, _flags(residual, sigmoid_decay, sigmoid_pregate), run_len,
+                                     _raw(stream))
+        if r is not None:
+            return _checked(r, "swr_uniform_backward")
     torch = _torch()
     problem = _problem_from(x, a, window, residual, run_len, sigmoid_decay, sigmoid_pregate)
     _same_layout(x, b, c, dy)

@@ -1,4 +1,5 @@
-"""Build the gfx950 HIP library ``paper_2512_13921_amd/libswr.so``.
+"""Build the gfx950 HIP library ``paper_2512_13921_amd/libswr.so`` and the
+native marshalling of its Python binding, ``paper_2512_13921_amd/_binding.so``.
 
 Usage: ``python -m paper_2512_13921_amd.build`` (or ``python paper_2512_13921_amd/build.py``).
 Cross-compiles on a machine without a GPU.
@@ -13,6 +14,8 @@ import tempfile
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libswr.so")
+BINDING = os.path.join(HERE, "_binding.so")
+BINDING_SOURCE = os.path.join(CSRC, "swr_binding.cpp")
 SOURCES = [os.path.join(CSRC, n) for n in ("swr_api.cpp", "swr_kernels.hip", "swr_uniform.hip", "swr_groups.hip",
                                             "swr_noalloc.hip", "swr_chain.hip")]
 HEADERS = [os.path.join(CSRC, "swr_launch.h"), os.path.join(CSRC, "swr_device.h"),
@@ -77,8 +80,32 @@ def _messages(res) -> list:
             if not any(n in ln for n in noise) and not quoted.match(ln)]
 
 
+def binding_command(out: str) -> list:
+    """The host compiler's line for the binding's extension module."""
+    import sysconfig
+    from torch.utils import cpp_extension
+    lib = cpp_extension.library_paths()[0]
+    return ["g++", "-std=c++17", "-O2", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+            *(f"-isystem{p}" for p in (*cpp_extension.include_paths(), "/opt/rocm/include",
+                                       sysconfig.get_paths()["include"])),
+            BINDING_SOURCE, f"-L{lib}", f"-Wl,-rpath,{lib}", "-ltorch_python", "-ltorch", "-ltorch_cpu", "-lc10",
+            "-lc10_hip", "-o", out]
+
+
+def build_binding(verbose: bool = False) -> str:
+    cmd = binding_command(BINDING + ".tmp")
+    if verbose:
+        print(" ".join(cmd))
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    if res.returncode != 0:
+        raise RuntimeError("g++ failed on the binding:\n" + res.stdout + res.stderr)
+    os.replace(BINDING + ".tmp", BINDING)
+    return BINDING
+
+
 def build(verbose: bool = False, extra=(), out: str = LIB) -> str:
-    """Compiles every source to an object (in parallel), then links ``out``."""
+    """Compiles every source to an object (in parallel), then links ``out``
+    (and, with the library in its place, builds the binding's extension)."""
     with tempfile.TemporaryDirectory() as tmp:
         objs = [os.path.join(tmp, os.path.basename(s) + ".o") for s in SOURCES]
         procs = []
@@ -108,6 +135,8 @@ def build(verbose: bool = False, extra=(), out: str = LIB) -> str:
         if res.returncode != 0:
             raise RuntimeError("hipcc link failed:\n" + "\n".join(_messages(res)))
     os.replace(out + ".tmp", out)
+    if out == LIB:
+        build_binding(verbose)
     return out
 
 
