@@ -69,8 +69,8 @@ int64_t plan_run_len(int64_t T, int64_t units, int64_t step, int64_t halo, const
 // cost less than further halos.  4 waves: two (three of packed heads, 165 VGPRs,
 // and of float32 heads of 64, 150), or four of the narrow ones, and
 // runs of 256 tokens once those make several rounds (512 for heads of 128 and
-// bf16 heads of 64, 128 where a token moves the most bytes: float32 with a
-// decay per channel), or twice that for bf16 heads of 64 or more without saved
+// bf16 heads of 64, 128 for float32 lanes of 1 or 2 channels and with a decay per
+// channel), or twice that for bf16 heads of 64 or more without saved
 // carriers, whose halo is a step longer.  Against fixed grids of 256, 1024 (128
 // channels) and 8192 workgroups, bf16, saved carriers: D 64, l 64, 16 heads of
 // 16384 tokens 68.2 -> 48 us, of 65536 235 -> 211; a decay per channel, D 128,
@@ -136,7 +136,7 @@ struct Resolved {
 
 Sweep bwd_sweep(const Resolved& r, bool recompute) {
     if (r.bwd.tw * r.bwd.hw == 8) return {r.cpl >= 4 || (r.cpl == 2 && recompute) ? 256 : 512, 0};
-    if (r.cpl <= 2) return {1024, 256};
+    if (r.cpl <= 2) return {1024, r.es == 4 ? 128 : 256};
     if (r.pack > 1) return {recompute ? 512 : 768, 256};
     const int64_t len = r.cpl == 8 || (r.es == 2 && !r.pc) ? 512 : r.pc && r.es == 4 ? 128 : 256;
     // (a decay per channel: heads in four parts, or that leave lanes idle, ran
@@ -184,8 +184,16 @@ int resolve(const swr_problem_t* p, Resolved* r, bool allow_pack = true, bool al
     // Heads of 16 or 32 channels stored next to each other run as packed
     // 64-channel virtual heads on the per-channel kernels (a lane slice of one
     // such head would be 2-4 bytes); the caller's pointers may still veto it
-    // (alignment), see resolve_for.
-    if (allow_pack && !r->pc && (p->D == 16 || p->D == 32) && p->H % (64 / p->D) == 0 && p->sx_h == p->D) {
+    // (alignment), see resolve_for.  A head count that does not divide leaves
+    // lanes of the last virtual head idle, which still beats the narrow slices
+    // once there is work for the machine (bf16, 2 x 7 heads of 16, T 65536, l
+    // 64: forward 78 -> 34 us, backward 60 -> 43; 2 x 5, T 4096 7.8 -> 7.5; 2 x 3,
+    // T 4096 would take 7.3 against 6.6); in float32 the forward only (2 x 7, T
+    // 65536 78 -> 53; the backward of 2 x 5 would take 91 against 80).  A forced
+    // run length, tuned with the heads one by one, keeps them so.
+    if (allow_pack && !r->pc && (p->D == 16 || p->D == 32) && p->sx_h == p->D &&
+        (p->H % (64 / p->D) == 0 ||
+         (p->H >= 2 && p->run_len == 0 && (r->es == 2 || allow_pair) && p->B * p->H * p->T >= 32768))) {
         r->pack = (int)(64 / p->D);
         r->dk = 64;
     }
@@ -206,7 +214,7 @@ int resolve(const swr_problem_t* p, Resolved* r, bool allow_pack = true, bool al
     if (r->pair) r->dk = 128;
     r->cpl = r->dk / 16;
     r->nlane = r->pack > 1 || r->pair ? 16 : r->dv / r->cpl;
-    r->hv = r->pack > 1 ? p->H / r->pack : r->pair ? p->H / 2 : p->H << r->hshift;
+    r->hv = r->pack > 1 ? (p->H + r->pack - 1) / r->pack : r->pair ? p->H / 2 : p->H << r->hshift;
     r->vbytes = std::min<int64_t>(16, (int64_t)(r->dk / 16) * r->es);
     r->bwd = swr::bwd_shape(p->block, r->hv);
     r->fwd = swr::fwd_shape(p->block, r->hv);
@@ -487,10 +495,9 @@ int64_t bwd_agg_len(const swr_problem_t* p, const Resolved& r) {
 // Workspace of the exact recurrence, in float32 elements: per (batch, head)
 // and aggregate run, the run's aggregate end state (D), the value entering
 // the run (D) and the run's decay product (1, or D for a per-channel decay),
-// for the largest of the launches' run counts.  Where the one-pass chain is
-// the other route (one decay per head, heads not packed) the arrays start
-// past its two counters, so that the count of waits that gave up reads zero
-// whichever route a call took.
+// for the largest of the launches' run counts.  With one decay per head the
+// arrays start past the one-pass chain's two counters, so that the count of
+// waits that gave up reads zero whichever route a call took.
 struct ExactWs {
     int64_t nr;       // runs per sequence the workspace is laid out for
     int64_t head;     // float32 elements before the arrays
@@ -501,7 +508,7 @@ ExactWs exact_ws(const swr_problem_t* p, const Resolved& r) {
     ExactWs w;
     const int64_t na = r.empty ? 0 : (p->T + bwd_agg_len(p, r) - 1) / bwd_agg_len(p, r);
     w.nr = std::max(std::max(r.nruns, r.nruns_f), na);
-    w.head = !r.empty && !r.pc && r.pack == 1 ? 16 : 0;
+    w.head = !r.empty && !r.pc ? 16 : 0;
     // a per-channel decay has one run decay product per channel
     w.floats = w.head + p->B * p->H * w.nr * (2 * p->D + (r.pc || r.pack > 1 ? p->D : 1));
     return w;
@@ -684,6 +691,11 @@ int swr::exact_forward_impl(const swr_problem_t* p, const void* x, const void* a
     int rc = resolve_for(p, &r, {x, b, c, (const void*)y});
     if (rc != SWR_OK) return rc;
     if (!r.natural) return SWR_ERR_UNSUPPORTED;
+    // (packed heads of a count that fills no whole virtual head: the chain of
+    // the heads one by one may fit the static array where the stages do not)
+    if (scratch && r.pack > 1 && p->H % r.pack && exact_ws(p, r).floats * 4 > scratch_bytes &&
+        (rc = resolve(p, &r, false)) != SWR_OK)
+        return rc;
     ExactWs w = exact_ws(p, r);
     // the library's static array may hold the three stages' arrays but not the
     // one pass's: the allocation-free call then runs the three stages.  bf16
@@ -791,7 +803,7 @@ int swr::exact_forward_impl(const swr_problem_t* p, const void* x, const void* a
     if (w.floats > 0) exact_arrays(p, w, workspace, &wv, &wc, &wp);
     swr::Params k = make_params(p, r, false);
     k.x = x; k.a = a; k.b = b; k.c = c;
-    if (use_chain(p, r) && (single || w.head)) k.chain_ctr = (int32_t*)workspace;
+    if (w.head || (single && use_chain(p, r))) k.chain_ctr = (int32_t*)workspace;
     if (single) {   // stage III alone, from h0
         set_one_run(p, &k, r.fwd.tw, r.hv / r.fwd.hw);
         k.carry = h0; k.h_last = h_last;
@@ -878,7 +890,7 @@ int swr_exact_backward(const swr_problem_t* p, const void* x, const void* a, con
     if (w.floats > 0) exact_arrays(p, w, workspace, &wv, &wc, &wp);
     swr::Params k = make_params(p, r, true);
     k.x = x; k.a = a; k.b = b; k.c = c; k.dy = dy;
-    if (use_chain_bwd(p, r)) k.chain_ctr = (int32_t*)workspace;
+    if (w.head) k.chain_ctr = (int32_t*)workspace;
     if (single) {   // stage III alone, from dh_last
         set_one_run(p, &k, r.bwd.tw, r.hv / r.bwd.hw);
         k.carry = dh_last; k.dh0 = dh0; k.h0 = h0;

@@ -566,11 +566,13 @@ struct Geo {
     int lh;         // real head of this lane within the virtual head
     int lch;        // first channel of this lane within its real head
     bool ok;        // the lane holds channels (a virtual head of p.dv < D channels
-                    // leaves lanes n >= p.nlane idle)
+                    // leaves lanes n >= p.nlane idle; the last packed head those
+                    // of heads past p.H)
     __device__ Geo(int64_t vh, const Params& p, int n) {
         constexpr int D = CPL * SB;
         if constexpr (PK > 1) {
-            head = vh * PK; coff = 0; Dr = D / PK; lh = n / LPH; lch = (n % LPH) * CPL; ok = true;
+            head = vh * PK; coff = 0; Dr = D / PK; lh = n / LPH; lch = (n % LPH) * CPL;
+            ok = head + lh < p.H;
         } else {
             head = vh >> p.hshift; coff = (vh & ((1 << p.hshift) - 1)) * (int64_t)p.dv; Dr = p.dh;
             lh = 0; lch = (int)coff + n * CPL; ok = n < p.nlane;

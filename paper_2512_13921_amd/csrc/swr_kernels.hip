@@ -1281,7 +1281,7 @@ __global__ __launch_bounds__(TW * HW * 64, 3) void swr_fwd_pc_kernel(Params p) {
     const int64_t rs = p.sx_t * ES;
     const int64_t as = PK > 1 ? p.sa_t * ES : rs;
     const uint32_t loff = in_range(geo.ok, (uint32_t)(4 * grp) * (uint32_t)rs + (uint32_t)(n * CPL * ES));
-    const uint32_t aoffp = (uint32_t)(4 * grp) * (uint32_t)as + (uint32_t)(geo.lh * p.sa_h * ES);
+    const uint32_t aoffp = in_range(geo.ok, (uint32_t)(4 * grp) * (uint32_t)as + (uint32_t)(geo.lh * p.sa_h * ES));
     const bool want_y = MODE != kAggregate && p.y != nullptr;
     const int64_t hb = wk.b * p.H + geo.head;   // first real (batch, head) of the virtual head
     float* const vb = MODE != kAggregate && p.carriers ? p.carriers + hb * p.nblocks * geo.Dr : nullptr;
@@ -1293,7 +1293,7 @@ __global__ __launch_bounds__(TW * HW * 64, 3) void swr_fwd_pc_kernel(Params p) {
     if constexpr (MODE == kExact) {
         Row<IoF32, CPL> ci;
         ci.load(rsrc(p.carry + hb * p.agg_nruns * geo.Dr),
-                in_range(p.carry != nullptr, geo.off(p.agg_nruns, wk.t_begin / p.agg_len) * 4u));
+                in_range(p.carry != nullptr && geo.ok, geo.off(p.agg_nruns, wk.t_begin / p.agg_len) * 4u));
 #pragma unroll
         for (int m = 0; m < CPL; ++m) e[m] = ci.get(m);
         clear_time_outs(p);
@@ -1390,10 +1390,11 @@ __global__ __launch_bounds__(TW * HW * 64, 3) void swr_fwd_pc_kernel(Params p) {
     }
     if constexpr (MODE == kExact) {   // a single run's end state is the sequence's
         if (p.h_last)
-            store_row<IoF32, CPL>(rsrc(p.h_last + hb * geo.Dr), in_range(tw == 0 && grp == 0, geo.off(1, 0) * 4u), e);
+            store_row<IoF32, CPL>(rsrc(p.h_last + hb * geo.Dr),
+                                  in_range(tw == 0 && grp == 0 && geo.ok, geo.off(1, 0) * 4u), e);
     }
     if constexpr (MODE == kAggregate) {   // the run's end state from zero and decay products
-        const uint32_t o = in_range(tw == 0 && grp == 0, geo.off(p.nruns, wk.run) * 4u);
+        const uint32_t o = in_range(tw == 0 && grp == 0 && geo.ok, geo.off(p.nruns, wk.run) * 4u);
         store_row<IoF32, CPL>(rsrc(p.agg_v + hb * p.nruns * geo.Dr), o, e);
         store_row<IoF32, CPL>(rsrc(p.agg_p + hb * p.nruns * geo.Dr), o, prod);
     }
@@ -1451,7 +1452,7 @@ __global__ __launch_bounds__(TW * HW * 64, 2) void swr_bwd_pc_kernel(Params p) {
     const int64_t as = PK > 1 ? p.sa_t * ES : rs;
     const int64_t das = PK > 1 ? p.sa_t * 4 : p.sx_t * 4;
     const uint32_t loff = in_range(geo.ok, (uint32_t)(4 * grp) * (uint32_t)rs + (uint32_t)(n * CPL * ES));
-    const uint32_t aoffp = (uint32_t)(4 * grp) * (uint32_t)as + (uint32_t)(geo.lh * p.sa_h * ES);
+    const uint32_t aoffp = in_range(geo.ok, (uint32_t)(4 * grp) * (uint32_t)as + (uint32_t)(geo.lh * p.sa_h * ES));
     const uint32_t daoff = PK > 1 ? (uint32_t)(4 * grp) * (uint32_t)das + (uint32_t)(geo.lh * p.sa_h * 4)
                                   : in_range(geo.ok, (uint32_t)(4 * grp) * (uint32_t)das + (uint32_t)(n * CPL * 4));
 
@@ -1462,7 +1463,7 @@ __global__ __launch_bounds__(TW * HW * 64, 2) void swr_bwd_pc_kernel(Params p) {
         Row<IoF32, CPL> ci;
         // the run's last aggregate
         ci.load(rsrc(p.carry + hb * p.agg_nruns * geo.Dr),
-                in_range(p.carry != nullptr, geo.off(p.agg_nruns, (wk.t_end - 1) / p.agg_len) * 4u));
+                in_range(p.carry != nullptr && geo.ok, geo.off(p.agg_nruns, (wk.t_end - 1) / p.agg_len) * 4u));
 #pragma unroll
         for (int m = 0; m < CPL; ++m) eps[m] = ci.get(m);
         clear_time_outs(p);
@@ -1552,7 +1553,7 @@ __global__ __launch_bounds__(TW * HW * 64, 2) void swr_bwd_pc_kernel(Params p) {
             const int64_t blk = (t0 >> p.lshift) - 1;
             Row<IoF32, CPL> vr;
             vr.load(rsrc(from_h0 ? p.h0 + hb * geo.Dr : vb),
-                    from_h0 ? in_range(live && p.h0 != nullptr, geo.off(1, 0) * 4u)
+                    from_h0 ? in_range(live && p.h0 != nullptr && geo.ok, geo.off(1, 0) * 4u)
                             : in_range(live && t0 > 0 && geo.ok, geo.off(p.nblocks, blk) * 4u));
 #pragma unroll
             for (int m = 0; m < CPL; ++m) in.v[m] = vr.get(m);
@@ -1765,7 +1766,7 @@ __global__ __launch_bounds__(TW * HW * 64, 2) void swr_bwd_pc_kernel(Params p) {
                 if (sig_a) tot *= sigmoid_slope(az[r]).ds;
                 __builtin_amdgcn_raw_buffer_store_b32(
                     __builtin_bit_cast(int, tot), rda,
-                    (int)in_range(t < wk.t_end && geo.lch == 0, daoff + (uint32_t)(r * das)), 0, kBwdStore);
+                    (int)in_range(t < wk.t_end && geo.lch == 0 && geo.ok, daoff + (uint32_t)(r * das)), 0, kBwdStore);
             } else {
                 store_row<IoF32, CPL, kBwdStore>(rda, in_range(t < wk.t_end, daoff + (uint32_t)(r * das)), vda);
             }
@@ -1773,7 +1774,8 @@ __global__ __launch_bounds__(TW * HW * 64, 2) void swr_bwd_pc_kernel(Params p) {
     }
     if constexpr (MODE == kExact) {   // what leaves a single run's first token leaves the sequence
         if (p.dh0)
-            store_row<IoF32, CPL>(rsrc(p.dh0 + hb * geo.Dr), in_range(tw == 0 && grp == 0, geo.off(1, 0) * 4u), eps);
+            store_row<IoF32, CPL>(rsrc(p.dh0 + hb * geo.Dr),
+                                  in_range(tw == 0 && grp == 0 && geo.ok, geo.off(1, 0) * 4u), eps);
     }
 }
 
@@ -1799,8 +1801,8 @@ __global__ __launch_bounds__(TW * 64, 2) void swr_bwd_pc_agg_kernel(Params p) {
     const char* ab = PK > 1 ? (const char*)p.a + (wk.b * p.sa_b + geo.head * p.sa_h) * ES : (const char*)p.a + xo;
     const int64_t rs = p.sx_t * ES;
     const int64_t as = PK > 1 ? p.sa_t * ES : rs;
-    const uint32_t loff = (uint32_t)(4 * grp) * (uint32_t)rs + (uint32_t)(n * CPL * ES);
-    const uint32_t aoffp = (uint32_t)(4 * grp) * (uint32_t)as + (uint32_t)(geo.lh * p.sa_h * ES);
+    const uint32_t loff = in_range(geo.ok, (uint32_t)(4 * grp) * (uint32_t)rs + (uint32_t)(n * CPL * ES));
+    const uint32_t aoffp = in_range(geo.ok, (uint32_t)(4 * grp) * (uint32_t)as + (uint32_t)(geo.lh * p.sa_h * ES));
     const int64_t hb = wk.b * p.H + geo.head;
 
     float eps[CPL], prod[CPL];
@@ -1850,7 +1852,7 @@ __global__ __launch_bounds__(TW * 64, 2) void swr_bwd_pc_agg_kernel(Params p) {
             }
         }
     }
-    const uint32_t o = in_range(tw == 0 && grp == 0, geo.off(p.nruns, wk.run) * 4u);
+    const uint32_t o = in_range(tw == 0 && grp == 0 && geo.ok, geo.off(p.nruns, wk.run) * 4u);
     store_row<IoF32, CPL>(rsrc(p.agg_v + hb * p.nruns * geo.Dr), o, eps);
     store_row<IoF32, CPL>(rsrc(p.agg_p + hb * p.nruns * geo.Dr), o, prod);
 }

@@ -1,0 +1,97 @@
+"""GPU parity of packed small heads where the head count does not fill the last
+64-channel virtual head (its other lanes idle): every path against the oracle,
+and nothing written past the real heads' outputs."""
+import numpy as np
+import pytest
+
+import oracle
+import workloads as W
+from parity import assert_close, check_full, run_gpu, to_device, to_host
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+CASES = [
+    # (B, T, H, D, block, dtype)
+    (2, 2500, 7, 16, 16, "bf16"),      # 35000 tokens of heads: padded
+    (1, 1000, 33, 16, 128, "bf16"),
+    (9, 2000, 2, 16, 64, "bf16"),
+    (3, 5461, 2, 16, 64, "f32"),       # 32766: the last that stays unpadded
+    (2, 8192, 2, 16, 64, "f32"),       # 32768: the forward alone
+    (3, 3700, 3, 32, 32, "bf16"),
+    (2, 3300, 5, 32, 128, "f32"),
+    (2, 300, 7, 16, 16, "bf16"),
+]
+
+
+@pytest.fixture(scope="module")
+def swr():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2512_13921_amd as lib
+    lib.load()
+    return lib
+
+
+@pytest.mark.parametrize("B,T,H,D,block,dtype", CASES)
+@pytest.mark.parametrize("carriers", [True, False])
+def test_odd_head_counts(swr, B, T, H, D, block, dtype, carriers):
+    prob = W.random_problem(181 + T + H, B, T, H, D, block, dtype, "sigmoid", 2.0)
+    y, grads = run_gpu(swr, prob, residual=True, carriers=carriers)
+    check_full(prob, y, grads, residual=True, what=f"packed odd {B}x{T}x{H}x{D} l{block} {dtype}")
+
+
+def test_odd_head_counts_featurised(swr):
+    prob = W.random_problem(182, 2, 3300, 5, 16, 32, "bf16", "sigmoid", 3.0, logits=True)
+    feat = dict(sigmoid_decay=True, sigmoid_pregate=True)
+    y, grads = run_gpu(swr, prob, **feat)
+    check_full(prob, y, grads, what="packed odd sigmoid", **feat)
+
+
+def _guarded(shape, dtype=torch.float32):
+    """A tensor of this shape inside a larger one, and the values around it."""
+    n = int(np.prod(shape))
+    buf = torch.full((n + 2048,), 7.0, dtype=dtype, device="cuda")
+    return buf[1024:1024 + n].view(shape), (buf[:1024], buf[1024 + n:])
+
+
+@pytest.mark.parametrize("B,T,H,D,block,dtype", CASES)
+def test_exact_odd_head_counts(swr, B, T, H, D, block, dtype):
+    prob = W.random_problem(183 + T + H, B, T, H, D, block, dtype, "sigmoid", 3.0)
+    x, a, b, c, dy = (to_device(getattr(prob, n), dtype) for n in ("x", "a", "b", "c", "dy"))
+    rng = np.random.default_rng(T)
+    h0, dhl = (rng.standard_normal((B, H, D)).astype(np.float32) for _ in range(2))
+    h0d, dhld = torch.from_numpy(h0).cuda(), torch.from_numpy(dhl).cuda()
+    y, gy = _guarded((B, T, H, D), x.dtype)
+    v, gv = _guarded((B, H, -(-T // block), D))
+    hl, gh = _guarded((B, H, D))
+    outs, guards = zip(*(_guarded(s, d) for s, d in (((B, T, H, D), x.dtype), ((B, T, H), torch.float32),
+                                                     ((B, T, H, D), x.dtype), ((B, T, H, D), x.dtype))))
+    swr.swr_exact_forward(x, a, b, c, block, h0=h0d, y=y, carriers=v, h_last=hl)
+    *_, dh0 = swr.swr_exact_backward(x, a, b, c, dy, v, block, h0=h0d, dh_last=dhld, outputs=outs, want_dh0=True)
+    torch.cuda.synchronize()
+    for g in (gy, gv, gh) + guards:
+        assert all(bool((t == 7.0).all()) for t in g)
+    ref_y, ref_hl = oracle.exact_forward(prob.x, prob.a, prob.b, prob.c, h0)
+    refs = oracle.exact_backward(prob.x, prob.a, prob.b, prob.c, prob.dy, h0, dhl)
+    assert_close(to_host(y), ref_y, dtype, "y")
+    assert_close(to_host(hl), ref_hl, dtype, "h_last")
+    for name, got, ref in zip(("dx", "da", "db", "dc", "dh0"), tuple(outs) + (dh0,), refs):
+        assert_close(to_host(got), ref, dtype, name)
+
+
+@pytest.mark.parametrize("B,T,H,D,block,dtype", CASES)
+def test_odd_head_counts_write_only_their_outputs(swr, B, T, H, D, block, dtype):
+    prob = W.random_problem(184 + T + H, B, T, H, D, block, dtype, "sigmoid", 2.0)
+    x, a, b, c, dy = (to_device(getattr(prob, n), dtype) for n in ("x", "a", "b", "c", "dy"))
+    y, gy = _guarded((B, T, H, D), x.dtype)
+    v, gv = _guarded((B, H, -(-T // block), D))
+    outs, guards = zip(*(_guarded(s, d) for s, d in (((B, T, H, D), x.dtype), ((B, T, H), torch.float32),
+                                                     ((B, T, H, D), x.dtype), ((B, T, H, D), x.dtype))))
+    swr.swr_forward(x, a, b, c, block, y=y, carriers=v)
+    swr.swr_backward(x, a, b, c, dy, v, block, outputs=outs)
+    torch.cuda.synchronize()
+    for g in (gy, gv) + guards:
+        assert all(bool((t == 7.0).all()) for t in g)
+    check_full(prob, y, outs, what="packed odd guarded")
