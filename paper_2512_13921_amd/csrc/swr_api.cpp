@@ -152,9 +152,10 @@ void plan_backward(const swr_problem_t* p, Resolved* r, bool recompute) {
         r->run_len = p->run_len;
     else if (r->empty)
         r->run_len = r->step;
+    else if (r->pack > 1 && r->es == 4 && r->bwd.tw == 4)   // (within 7% of the plan either way)
+        r->run_len = pick_run_len(p->T, groups, r->step, 8192);
     else
-        r->run_len = plan_run_len(p->T, groups, r->step, p->block,
-                                  bwd_sweep(*r, recompute));
+        r->run_len = plan_run_len(p->T, groups, r->step, p->block, bwd_sweep(*r, recompute));
     r->nruns = r->empty ? 0 : (p->T + r->run_len - 1) / r->run_len;
     r->nwork = groups * r->nruns;
 }
