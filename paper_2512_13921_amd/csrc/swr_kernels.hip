@@ -87,6 +87,7 @@ __global__ __launch_bounds__(TW * HW * 64, 3) void swr_fwd_kernel(Params p) {
     constexpr bool GG = MODE == kGrouped;
     constexpr bool PAIR = MODE == kPaired;
     constexpr bool SWR = MODE == kSwr || GG || PAIR;
+    constexpr int kGateLoad = GG ? kSharedGateLoad : kFwdLoad;   // of b and c
     constexpr int NH = PAIR ? 2 : 1;   // heads per kernel head
     const int sig_a = FEAT ? p.sig_a : 0, sig_b = FEAT ? p.sig_b : 0;   // fused featurisation
     constexpr int NW = TW * HW;
@@ -181,8 +182,8 @@ __global__ __launch_bounds__(TW * HW * 64, 3) void swr_fwd_kernel(Params p) {
         for (int r = 0; r < 4; ++r) {
             const uint32_t o = loff + (uint32_t)(r * rs), og = goff + (uint32_t)(r * gs);
             LR::template issue<kFwdLoad>(rx, in_range(ok_xb(tr0 + r), o), s_tile[wv][0][r]);
-            LR::template issue<kFwdLoad>(rb, in_range(ok_xb(tr0 + r), og), s_tile[wv][1][r]);
-            LR::template issue<kFwdLoad>(rc, in_range(ok_c(tr0 + r), og), s_tile[wv][2][r]);
+            LR::template issue<kGateLoad>(rb, in_range(ok_xb(tr0 + r), og), s_tile[wv][1][r]);
+            LR::template issue<kGateLoad>(rc, in_range(ok_c(tr0 + r), og), s_tile[wv][2][r]);
         }
     };
     if constexpr (PREFETCH) {
@@ -221,8 +222,8 @@ __global__ __launch_bounds__(TW * HW * 64, 3) void swr_fwd_kernel(Params p) {
                 const int64_t t = tr0 + r;
                 const uint32_t o = loff + (uint32_t)(r * rs), og = goff + (uint32_t)(r * gs);
                 xr[r].template load<kFwdLoad>(rx, in_range(ok_xb(t), o));
-                br[r].template load<kFwdLoad>(rb, in_range(ok_xb(t), og));
-                cr[r].template load<kFwdLoad>(rc, in_range(ok_c(t), og));
+                br[r].template load<kGateLoad>(rb, in_range(ok_xb(t), og));
+                cr[r].template load<kGateLoad>(rc, in_range(ok_c(t), og));
             }
         }
         const int64_t ta = r0 + n;
