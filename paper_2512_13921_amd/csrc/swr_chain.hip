@@ -266,8 +266,8 @@ __global__ __launch_bounds__(kChainTW * 64, (chain_waves_per_simd<IO, CPL>())) v
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const uint32_t o = in_range(tr0 + r < p.T, loff + (uint32_t)(r * rs));
-                xr[r].template load<kFwdLoad>(rx, o);
-                br[r].template load<kFwdLoad>(rb, o);
+                xr[r].template load<Stream<IO, CPL>::load>(rx, o);
+                br[r].template load<Stream<IO, CPL>::load>(rb, o);
             }
         }
         const bool a_ok = r0 + n < p.T;
@@ -300,7 +300,7 @@ __global__ __launch_bounds__(kChainTW * 64, (chain_waves_per_simd<IO, CPL>())) v
             const __amdgpu_buffer_rsrc_t rc = rsrc((const char*)p.c + xo + r0 * rs);
 #pragma unroll
             for (int r = 0; r < 4; ++r)
-                cr[r].template load<kFwdLoad>(rc, in_range(tr0 + r < p.T, loff + (uint32_t)(r * rs)));
+                cr[r].template load<Stream<IO, CPL>::load>(rc, in_range(tr0 + r < p.T, loff + (uint32_t)(r * rs)));
         }
         lds_barrier();
 
@@ -352,7 +352,8 @@ __global__ __launch_bounds__(kChainTW * 64, (chain_waves_per_simd<IO, CPL>())) v
             const __amdgpu_buffer_rsrc_t rx = rsrc((const char*)p.x + xo + r0 * rs);
 #pragma unroll
             for (int r = 0; r < 4; ++r)
-                xres[r].template load<kFwdLoad>(rx, in_range(p.residual && tr0 + r < p.T, loff + (uint32_t)(r * rs)));
+                xres[r].template load<Stream<IO, CPL>::load>(
+                    rx, in_range(p.residual && tr0 + r < p.T, loff + (uint32_t)(r * rs)));
         } else {
 #pragma unroll
             for (int r = 0; r < 4; ++r) xres[r] = xr[r];
@@ -365,7 +366,7 @@ __global__ __launch_bounds__(kChainTW * 64, (chain_waves_per_simd<IO, CPL>())) v
                 yv[m] = cr[r].get(m) * __builtin_fmaf(dk.G[r], e[m], Wo[m][r]);
                 if (p.residual) yv[m] += xres[r].get(m);
             }
-            store_row<IO, CPL, kFwdStore>(ry, in_range(tr0 + r < p.T, loff + (uint32_t)(r * rs)), yv);
+            store_row<IO, CPL, Stream<IO, CPL>::store>(ry, in_range(tr0 + r < p.T, loff + (uint32_t)(r * rs)), yv);
         }
         // the exact state at the end of a block that ends with this sub-block
         // (a block longer than a chunk that the sequence's end cuts short ends in the last chunk)
@@ -441,8 +442,8 @@ __global__ __launch_bounds__(kChainTW * 64, 4) void swr_fwd_chain_pair_kernel(Pa
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const uint32_t o = in_range(tr0 + r < p.T, loff + (uint32_t)(r * rs));
-                xr[r].template load<kFwdLoad>(rx, o);
-                br[r].template load<kFwdLoad>(rb, o);
+                xr[r].template load<Stream<IO, CPL>::load>(rx, o);
+                br[r].template load<Stream<IO, CPL>::load>(rb, o);
             }
         }
         const bool a_ok = r0 + n < p.T;
@@ -474,7 +475,7 @@ __global__ __launch_bounds__(kChainTW * 64, 4) void swr_fwd_chain_pair_kernel(Pa
             const __amdgpu_buffer_rsrc_t rc = rsrc((const char*)p.c + xo + r0 * rs);
 #pragma unroll
             for (int r = 0; r < 4; ++r)
-                cr[r].template load<kFwdLoad>(rc, in_range(tr0 + r < p.T, loff + (uint32_t)(r * rs)));
+                cr[r].template load<Stream<IO, CPL>::load>(rc, in_range(tr0 + r < p.T, loff + (uint32_t)(r * rs)));
         }
         lds_barrier();
 
@@ -520,7 +521,8 @@ __global__ __launch_bounds__(kChainTW * 64, 4) void swr_fwd_chain_pair_kernel(Pa
             const __amdgpu_buffer_rsrc_t rx = rsrc((const char*)p.x + xo + r0 * rs);
 #pragma unroll
             for (int r = 0; r < 4; ++r)
-                xres[r].template load<kFwdLoad>(rx, in_range(p.residual && tr0 + r < p.T, loff + (uint32_t)(r * rs)));
+                xres[r].template load<Stream<IO, CPL>::load>(
+                    rx, in_range(p.residual && tr0 + r < p.T, loff + (uint32_t)(r * rs)));
         }
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
@@ -531,7 +533,7 @@ __global__ __launch_bounds__(kChainTW * 64, 4) void swr_fwd_chain_pair_kernel(Pa
                 yv[m] = cr[r].get(m) * __builtin_fmaf(Gl[r], e[m], W[r]);
                 if (p.residual) yv[m] += xres[r].get(m);
             }
-            store_row<IO, CPL, kFwdStore>(ry, in_range(tr0 + r < p.T, loff + (uint32_t)(r * rs)), yv);
+            store_row<IO, CPL, Stream<IO, CPL>::store>(ry, in_range(tr0 + r < p.T, loff + (uint32_t)(r * rs)), yv);
         }
         // the exact state at the end of a block that ends with this sub-block
         // (a block longer than a chunk that the sequence's end cuts short ends in the last chunk)
@@ -611,9 +613,9 @@ __global__ __launch_bounds__(kChainTW * 64, (CPL == 4 ? 4 : 2)) void swr_fwd_cha
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const uint32_t o = in_range(tr0 + r < p.T, loff + (uint32_t)(r * rs));
-                xr[r].template load<kFwdLoad>(rx, o);
-                br[r].template load<kFwdLoad>(rb, o);
-                if constexpr (PK == 1) ar[r].template load<kFwdLoad>(ra, o);
+                xr[r].template load<Stream<IO, CPL>::load>(rx, o);
+                br[r].template load<Stream<IO, CPL>::load>(rb, o);
+                if constexpr (PK == 1) ar[r].template load<Stream<IO, CPL>::load>(ra, o);
             }
             if constexpr (PK > 1) {
                 float az[4];
@@ -649,7 +651,7 @@ __global__ __launch_bounds__(kChainTW * 64, (CPL == 4 ? 4 : 2)) void swr_fwd_cha
             const __amdgpu_buffer_rsrc_t rc = rsrc((const char*)p.c + xo + r0 * rs);
 #pragma unroll
             for (int r = 0; r < 4; ++r)
-                cr[r].template load<kFwdLoad>(rc, in_range(tr0 + r < p.T, loff + (uint32_t)(r * rs)));
+                cr[r].template load<Stream<IO, CPL>::load>(rc, in_range(tr0 + r < p.T, loff + (uint32_t)(r * rs)));
         }
         lds_barrier();
 
@@ -706,7 +708,7 @@ __global__ __launch_bounds__(kChainTW * 64, (CPL == 4 ? 4 : 2)) void swr_fwd_cha
                 yv[m] = cr[r].get(m) * __builtin_fmaf(G[r][m], e[m], W[r][m]);
                 if (p.residual) yv[m] += xr[r].get(m);
             }
-            store_row<IO, CPL, kFwdStore>(ry, in_range(tr0 + r < p.T, loff + (uint32_t)(r * rs)), yv);
+            store_row<IO, CPL, Stream<IO, CPL>::store>(ry, in_range(tr0 + r < p.T, loff + (uint32_t)(r * rs)), yv);
         }
         // the exact state at the end of a block that ends with this sub-block
         // (a block longer than a chunk that the sequence's end cuts short ends in the last chunk)

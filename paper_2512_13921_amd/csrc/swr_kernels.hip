@@ -87,7 +87,7 @@ __global__ __launch_bounds__(TW * HW * 64, 3) void swr_fwd_kernel(Params p) {
     constexpr bool GG = MODE == kGrouped;
     constexpr bool PAIR = MODE == kPaired;
     constexpr bool SWR = MODE == kSwr || GG || PAIR;
-    constexpr int kGateLoad = GG ? kSharedGateLoad : kFwdLoad;   // of b and c
+    constexpr int kGateLoad = GG ? kSharedGateLoad : Stream<IO, CPL>::load;   // of b and c
     constexpr int NH = PAIR ? 2 : 1;   // heads per kernel head
     const int sig_a = FEAT ? p.sig_a : 0, sig_b = FEAT ? p.sig_b : 0;   // fused featurisation
     constexpr int NW = TW * HW;
@@ -181,7 +181,7 @@ __global__ __launch_bounds__(TW * HW * 64, 3) void swr_fwd_kernel(Params p) {
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const uint32_t o = loff + (uint32_t)(r * rs), og = goff + (uint32_t)(r * gs);
-            LR::template issue<kFwdLoad>(rx, in_range(ok_xb(tr0 + r), o), s_tile[wv][0][r]);
+            LR::template issue<Stream<IO, CPL>::load>(rx, in_range(ok_xb(tr0 + r), o), s_tile[wv][0][r]);
             LR::template issue<kGateLoad>(rb, in_range(ok_xb(tr0 + r), og), s_tile[wv][1][r]);
             LR::template issue<kGateLoad>(rc, in_range(ok_c(tr0 + r), og), s_tile[wv][2][r]);
         }
@@ -221,7 +221,7 @@ __global__ __launch_bounds__(TW * HW * 64, 3) void swr_fwd_kernel(Params p) {
             for (int r = 0; r < 4; ++r) {
                 const int64_t t = tr0 + r;
                 const uint32_t o = loff + (uint32_t)(r * rs), og = goff + (uint32_t)(r * gs);
-                xr[r].template load<kFwdLoad>(rx, in_range(ok_xb(t), o));
+                xr[r].template load<Stream<IO, CPL>::load>(rx, in_range(ok_xb(t), o));
                 br[r].template load<kGateLoad>(rb, in_range(ok_xb(t), og));
                 cr[r].template load<kGateLoad>(rc, in_range(ok_c(t), og));
             }
@@ -332,7 +332,8 @@ __global__ __launch_bounds__(TW * HW * 64, 3) void swr_fwd_kernel(Params p) {
                 yv[m] = cr[r].get(m) * hv;
                 if (p.residual) yv[m] += xr[r].get(m);
             }
-            store_row<IO, CPL, kFwdStore>(ry, in_range(t >= wk.t_begin && t < wk.t_end, loff + (uint32_t)(r * rs)), yv);
+            store_row<IO, CPL, Stream<IO, CPL>::store>(
+                ry, in_range(t >= wk.t_begin && t < wk.t_end, loff + (uint32_t)(r * rs)), yv);
         }
     }
     if constexpr (MODE == kExact) {   // a single run's end state is the sequence's
@@ -839,8 +840,8 @@ __global__ __launch_bounds__(TW * 64, 2) void swr_bwd_agg_kernel(Params p) {
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const uint32_t o = in_range(tr0 + r < wk.t_end, loff + (uint32_t)(r * rs));
-            cr[r].template load<kAggLoad>(rc, o);
-            dyr[r].template load<kAggLoad>(rdy, o);
+            cr[r].template load<Stream<IO, CPL>::agg>(rc, o);
+            dyr[r].template load<Stream<IO, CPL>::agg>(rdy, o);
         }
         float a_n = load_scalar<IO, kAggLoad>(rsrc(ab + r0 * as), in_range(r0 + n < wk.t_end, aoff));
         if (sig_a) a_n = sigmoid(a_n);
@@ -1313,10 +1314,10 @@ __global__ __launch_bounds__(TW * HW * 64, 3) void swr_fwd_pc_kernel(Params p) {
             const int64_t t = tr0 + r;
             const uint32_t o = loff + (uint32_t)(r * rs);
             const bool in_xb = t >= t_lo && t < wk.t_end;
-            xr[r].template load<kFwdLoad>(rx, in_range(in_xb, o));
-            br[r].template load<kFwdLoad>(rb, in_range(in_xb, o));
-            if constexpr (PK == 1) ar[r].template load<kFwdLoad>(ra, in_range(in_xb, o));
-            cr[r].template load<kFwdLoad>(rc, in_range(want_y && t >= wk.t_begin && t < wk.t_end, o));
+            xr[r].template load<Stream<IO, CPL>::load>(rx, in_range(in_xb, o));
+            br[r].template load<Stream<IO, CPL>::load>(rb, in_range(in_xb, o));
+            if constexpr (PK == 1) ar[r].template load<Stream<IO, CPL>::load>(ra, in_range(in_xb, o));
+            cr[r].template load<Stream<IO, CPL>::load>(rc, in_range(want_y && t >= wk.t_begin && t < wk.t_end, o));
         }
         float av[4][CPL], u[4][CPL], W[4][CPL], G[4][CPL];
         if constexpr (PK > 1) {
@@ -1386,7 +1387,8 @@ __global__ __launch_bounds__(TW * HW * 64, 3) void swr_fwd_pc_kernel(Params p) {
                 yv[m] = cr[r].get(m) * (W[r][m] + G[r][m] * ein[m]);
                 if (p.residual) yv[m] += xr[r].get(m);
             }
-            store_row<IO, CPL, kFwdStore>(ry, in_range(t >= wk.t_begin && t < wk.t_end, loff + (uint32_t)(r * rs)), yv);
+            store_row<IO, CPL, Stream<IO, CPL>::store>(
+                ry, in_range(t >= wk.t_begin && t < wk.t_end, loff + (uint32_t)(r * rs)), yv);
         }
     }
     if constexpr (MODE == kExact) {   // a single run's end state is the sequence's
@@ -1819,9 +1821,9 @@ __global__ __launch_bounds__(TW * 64, 2) void swr_bwd_pc_agg_kernel(Params p) {
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const uint32_t o = in_range(tr0 + r < wk.t_end, loff + (uint32_t)(r * rs));
-            cr[r].template load<kAggLoad>(rc, o);
-            dyr[r].template load<kAggLoad>(rdy, o);
-            if constexpr (PK == 1) ar[r].template load<kAggLoad>(ra, o);
+            cr[r].template load<Stream<IO, CPL>::agg>(rc, o);
+            dyr[r].template load<Stream<IO, CPL>::agg>(rdy, o);
+            if constexpr (PK == 1) ar[r].template load<Stream<IO, CPL>::agg>(ra, o);
         }
         float av[4][CPL], dh[4][CPL], Dv[4][CPL], R[4][CPL];
         if constexpr (PK > 1) {   // 1 past the end

@@ -158,9 +158,9 @@ __global__ __launch_bounds__(TW * HW * 64, 2) void swr_uni_fwd_kernel(Params p) 
             for (int r = 0; r < 4; ++r) {
                 const bool ok = wk.valid && tr0 + r < wk.t_end;
                 const uint32_t o = loff + (uint32_t)(r * rs);
-                xr[r].template load<kFwdLoad>(rx, in_range(ok, o));
-                br[r].template load<kFwdLoad>(rb, in_range(ok, o));
-                cr[r].template load<kFwdLoad>(rc, in_range(ok && !halo, o));
+                xr[r].template load<Stream<IO, CPL>::load>(rx, in_range(ok, o));
+                br[r].template load<Stream<IO, CPL>::load>(rb, in_range(ok, o));
+                cr[r].template load<Stream<IO, CPL>::load>(rc, in_range(ok && !halo, o));
             }
         }
         const bool a_ok = wk.valid && r0 + n < wk.t_end;
@@ -224,7 +224,7 @@ __global__ __launch_bounds__(TW * HW * 64, 2) void swr_uni_fwd_kernel(Params p) 
                     yv[m] = cr[r].get(m) * (W[m][r] + dk.G[r] * (s[m] + gp * Q[r][m]));
                     if (p.residual) yv[m] += xr[r].get(m);
                 }
-                store_row<IO, CPL, kFwdStore>(
+                store_row<IO, CPL, Stream<IO, CPL>::store>(
                     ry, in_range(wk.valid && tr0 + r < wk.t_end, loff + (uint32_t)(r * rs)), yv);
             }
         }
