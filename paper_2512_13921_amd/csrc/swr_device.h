@@ -98,8 +98,7 @@ constexpr int kBwdStore = SWR_BWD_STORE_POLICY;
 // The streaming hint for rows of whole cache lines only: a row of fewer bytes
 // (heads of 16 channels, bf16 heads of 32, taken one at a time) shares its
 // lines with other heads' or tokens' rows, which the hint drops before those
-// are are
-// read, or writes out in parts (bf16, 8 x 15 heads, D 16, T 69905: uniform
+// are read, or writes out in parts (bf16, 8 x 15 heads, D 16, T 69905: uniform
 // forward 665 -> 378 us, a decay per channel 965 -> 555, heads stored head by
 // head 539 -> 422; D 32, T 34952, uniform 367 -> 270).
 template <class IO, int CPL>
