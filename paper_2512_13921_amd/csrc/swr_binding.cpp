@@ -103,14 +103,32 @@ bool problem(const at::Tensor& x, const at::Tensor& a, int64_t block, int64_t fl
     return true;
 }
 
+// Allocating and launching run without the interpreter's lock, so that other
+// Python threads go on where one waits for the allocator or a full queue.
+struct Unlocked {
+    PyThreadState* state = PyEval_SaveThread();
+    ~Unlocked() { PyEval_RestoreThread(state); }
+};
+
+template <typename F, typename... A>
+int call(F entry, A... args) {
+    const Unlocked unlocked;
+    return entry(args...);
+}
+
 void* ptr(const at::Tensor& t) { return t.defined() ? t.data_ptr() : nullptr; }
 float* fptr(const at::Tensor& t) { return (float*)ptr(t); }
 
-at::Tensor like(const at::Tensor& x) { return at::empty_strided(x.sizes(), x.strides(), x.options().requires_grad(false)); }
+at::Tensor like(const at::Tensor& x) {
+    const Unlocked unlocked;
+    return at::empty_strided(x.sizes(), x.strides(), x.options().requires_grad(false));
+}
 at::Tensor floats(const at::Tensor& x, at::IntArrayRef shape) {
+    const Unlocked unlocked;
     return at::empty(shape, x.options().dtype(at::kFloat).requires_grad(false));
 }
 at::Tensor decay_gradient(const at::Tensor& a) {
+    const Unlocked unlocked;
     return at::empty_strided(a.sizes(), a.strides(), a.options().dtype(at::kFloat).requires_grad(false));
 }
 
@@ -167,7 +185,7 @@ PyObject* forward(PyObject*, PyObject* const* v, Py_ssize_t) {
     if (!g.ok || (y.defined() && !same_layout(in.x, y)) || (s.defined() && !float_state(s, in.x, vs))) return none();
     if (!y.defined()) y = like(in.x);
     if (want && !s.defined()) s = floats(in.x, vs);
-    return results(abi.fn.forward(&p, ptr(in.x), ptr(in.a), ptr(in.b), ptr(in.c), ptr(y), fptr(s), st), {y, s});
+    return results(call(abi.fn.forward, &p, ptr(in.x), ptr(in.a), ptr(in.b), ptr(in.c), ptr(y), fptr(s), st), {y, s});
     END_HANDLE_TH_ERRORS
 }
 
@@ -184,7 +202,8 @@ PyObject* backward(PyObject*, PyObject* const* v, Py_ssize_t) {
     void* st = stream_of(*g.v, in.x, &g.ok);
     if (!g.ok || (s.defined() && !float_state(s, in.x, carrier_shape(p)))) return none();
     const at::Tensor dx = like(in.x), db = like(in.x), dc = like(in.x), da = decay_gradient(in.a);
-    return results(abi.fn.backward(&p, ptr(in.x), ptr(in.a), ptr(in.b), ptr(in.c), ptr(dy), fptr(s), ptr(dx), fptr(da),
+    return results(call(abi.fn.backward, &p, ptr(in.x), ptr(in.a), ptr(in.b), ptr(in.c), ptr(dy), fptr(s), ptr(dx),
+                          fptr(da),
                                    ptr(db), ptr(dc), st), {dx, da, db, dc});
     END_HANDLE_TH_ERRORS
 }
@@ -210,7 +229,7 @@ PyObject* exact_forward(PyObject*, PyObject* const* v, Py_ssize_t) {
     if (want_v) s = floats(in.x, carrier_shape(p));
     if (want_h) hl = floats(in.x, hs);
     const at::Tensor work = floats(in.x, {std::max<int64_t>(ws / 4, 1)});
-    return results(abi.fn.exact_forward(&p, ptr(in.x), ptr(in.a), ptr(in.b), ptr(in.c), fptr(h0), ptr(y), fptr(s),
+    return results(call(abi.fn.exact_forward, &p, ptr(in.x), ptr(in.a), ptr(in.b), ptr(in.c), fptr(h0), ptr(y), fptr(s),
                                         fptr(hl), ptr(work), st), {y, s, hl});
     END_HANDLE_TH_ERRORS
 }
@@ -238,7 +257,8 @@ PyObject* exact_backward(PyObject*, PyObject* const* v, Py_ssize_t) {
     at::Tensor dh0;
     if (want) dh0 = floats(in.x, hs);
     const at::Tensor work = floats(in.x, {std::max<int64_t>(ws / 4, 1)});
-    return results(abi.fn.exact_backward(&p, ptr(in.x), ptr(in.a), ptr(in.b), ptr(in.c), ptr(dy), fptr(h0), fptr(s),
+    return results(call(abi.fn.exact_backward, &p, ptr(in.x), ptr(in.a), ptr(in.b), ptr(in.c), ptr(dy), fptr(h0),
+                          fptr(s),
                                          fptr(dhl), ptr(dx), fptr(da), ptr(db), ptr(dc), fptr(dh0), ptr(work), st),
                    {dx, da, db, dc, dh0});
     END_HANDLE_TH_ERRORS
@@ -261,8 +281,10 @@ PyObject* step(PyObject*, PyObject* const* v, Py_ssize_t) {
         (y.defined() && !same_layout(in.x, y)))
         return none();
     if (!y.defined()) y = like(in.x);
-    const int rc = t0 < 0 ? abi.fn.exact_step(&p, ptr(in.x), ptr(in.a), ptr(in.b), ptr(in.c), ptr(y), fptr(state), st)
-                          : abi.fn.step(&p, t0, ptr(in.x), ptr(in.a), ptr(in.b), ptr(in.c), ptr(y), fptr(state), st);
+    const int rc = t0 < 0 ? call(abi.fn.exact_step, &p, ptr(in.x), ptr(in.a), ptr(in.b), ptr(in.c), ptr(y),
+          fptr(state), st)
+                          : call(abi.fn.step, &p, t0, ptr(in.x), ptr(in.a), ptr(in.b), ptr(in.c), ptr(y), fptr(state),
+                                st);
     return results(rc, {y});
     END_HANDLE_TH_ERRORS
 }
@@ -278,7 +300,7 @@ PyObject* decode_state(PyObject*, PyObject* const* v, Py_ssize_t) {
     void* st = stream_of(*g.v, x, &g.ok);
     if (!g.ok || !float_state(s, x, carrier_shape(p))) return none();
     const at::Tensor state = floats(x, {p.B, p.H, 2, p.D});
-    return results(abi.fn.decode_state(&p, ptr(a), fptr(s), fptr(state), st), {state});
+    return results(call(abi.fn.decode_state, &p, ptr(a), fptr(s), fptr(state), st), {state});
     END_HANDLE_TH_ERRORS
 }
 
@@ -293,7 +315,7 @@ PyObject* uniform_forward(PyObject*, PyObject* const* v, Py_ssize_t) {
     void* st = stream_of(*g.v, in.x, &g.ok);
     if (!g.ok) return none();
     const at::Tensor y = like(in.x);
-    return results(abi.fn.uniform_forward(&p, ptr(in.x), ptr(in.a), ptr(in.b), ptr(in.c), ptr(y), st), {y});
+    return results(call(abi.fn.uniform_forward, &p, ptr(in.x), ptr(in.a), ptr(in.b), ptr(in.c), ptr(y), st), {y});
     END_HANDLE_TH_ERRORS
 }
 
@@ -309,7 +331,8 @@ PyObject* uniform_backward(PyObject*, PyObject* const* v, Py_ssize_t) {
     void* st = stream_of(*g.v, in.x, &g.ok);
     if (!g.ok) return none();
     const at::Tensor dx = like(in.x), db = like(in.x), dc = like(in.x), da = decay_gradient(in.a);
-    return results(abi.fn.uniform_backward(&p, ptr(in.x), ptr(in.a), ptr(in.b), ptr(in.c), ptr(dy), ptr(dx), fptr(da),
+    return results(call(abi.fn.uniform_backward, &p, ptr(in.x), ptr(in.a), ptr(in.b), ptr(in.c), ptr(dy), ptr(dx),
+                          fptr(da),
                                            ptr(db), ptr(dc), st), {dx, da, db, dc});
     END_HANDLE_TH_ERRORS
 }
@@ -337,7 +360,7 @@ PyObject* forward_shared_gates(PyObject*, PyObject* const* v, Py_ssize_t) {
     const at::Tensor y = like(in.x);
     at::Tensor s;
     if (want) s = floats(in.x, carrier_shape(p));
-    return results(abi.fn.forward_shared_gates(&p, group, in.b.strides().data(), ptr(in.x), ptr(in.a), ptr(in.b),
+    return results(call(abi.fn.forward_shared_gates, &p, group, in.b.strides().data(), ptr(in.x), ptr(in.a), ptr(in.b),
                                                ptr(in.c), ptr(y), fptr(s), st), {y, s});
     END_HANDLE_TH_ERRORS
 }
@@ -358,7 +381,7 @@ PyObject* backward_shared_gates(PyObject*, PyObject* const* v, Py_ssize_t) {
     const at::Tensor dx = like(in.x), db = like(in.b), dc = like(in.b), da = decay_gradient(in.a);
     at::Tensor work;
     if (ws > 0) work = floats(in.x, {ws / 4});
-    return results(abi.fn.backward_shared_gates(&p, group, in.b.strides().data(), ptr(in.x), ptr(in.a), ptr(in.b),
+    return results(call(abi.fn.backward_shared_gates, &p, group, in.b.strides().data(), ptr(in.x), ptr(in.a), ptr(in.b),
                                                 ptr(in.c), ptr(dy), fptr(s), ptr(dx), fptr(da), ptr(db), ptr(dc),
                                                 ptr(work), st), {dx, da, db, dc});
     END_HANDLE_TH_ERRORS
