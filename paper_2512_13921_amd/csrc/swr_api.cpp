@@ -160,6 +160,16 @@ void plan_backward(const swr_problem_t* p, Resolved* r, bool recompute) {
     r->nwork = groups * r->nruns;
 }
 
+// Whether every 32-bit lane offset of packed heads stays below 2^31 bytes: a
+// lane adds its head's share of a virtual head to 16 tokens' rows, (pack - 1)
+// head strides of a / da and pack heads' carriers (x's head stride is D; the
+// exact recurrence's arrays have no more runs than there are blocks, or 4096).
+bool packed_offsets_fit(const swr_problem_t* p, int64_t pack) {
+    const int64_t lim = 0x7fffffffLL;
+    return p->sa_h >= 0 && p->sa_h <= lim / (4 * (pack - 1)) && p->sa_t >= 0 &&
+           p->sa_t <= (lim - (pack - 1) * p->sa_h * 4) / 64 && p->T / p->block < lim / (pack * p->D * 4);
+}
+
 int resolve(const swr_problem_t* p, Resolved* r, bool allow_pack = true, bool allow_pair = false) {
     if (!p) return SWR_ERR_NULL;
     if (p->abi_version != SWR_ABI_VERSION) return SWR_ERR_VERSION;
@@ -192,7 +202,7 @@ int resolve(const swr_problem_t* p, Resolved* r, bool allow_pack = true, bool al
     // T 4096 would take 7.3 against 6.6); in float32 the forward only (2 x 7, T
     // 65536 78 -> 53; the backward of 2 x 5 would take 91 against 80).  A forced
     // run length, tuned with the heads one by one, keeps them so.
-    if (allow_pack && !r->pc && (p->D == 16 || p->D == 32) && p->sx_h == p->D &&
+    if (allow_pack && !r->pc && (p->D == 16 || p->D == 32) && p->sx_h == p->D && packed_offsets_fit(p, 64 / p->D) &&
         (p->H % (64 / p->D) == 0 ||
          (p->H >= 2 && p->run_len == 0 && (r->es == 2 || allow_pair) && p->B * p->H * p->T >= 32768))) {
         r->pack = (int)(64 / p->D);

@@ -35,3 +35,36 @@ def test_uniform_backward_fits_one_round(B, H, T):
     i = _info(B, T, H, 64, 128, uniform=True)
     assert i["bwd_workgroups"] <= 256
     assert i["bwd_run_len"] % 128 == 0
+
+
+# Packed small heads: a lane's 32-bit offsets add its head's share of a, da and
+# the carriers.  Past 2^31 bytes the heads run one by one, whose bases are 64-bit.
+
+def _packed(B, T, H, D, block, dtype=swr.SWR_DTYPE_BF16, sa_t=None, sa_h=None):
+    sa_t = H if sa_t is None else sa_t
+    sa_h = 1 if sa_h is None else sa_h
+    p = swr.make_problem(B, T, H, D, block, dtype, (T * H * D, H * D, D), (max(T * sa_t, H * sa_h), sa_t, sa_h))
+    i = swr.swr_launch_info(p)
+    units = i["bwd_workgroups"] // -(-T // i["bwd_run_len"])
+    assert units in (B * H, B * -(-H * D // 64))
+    return units == B * -(-H * D // 64)
+
+
+@pytest.mark.parametrize("H,D", [(3, 16), (4, 16), (7, 16), (3, 32), (2, 32)])
+def test_packed_heads_bound_the_decays_offsets(H, D):
+    lim, pack = 2 ** 31 - 1, 64 // D
+    last = (lim - 64) // (4 * (pack - 1))               # 16 tokens of stride 1 and the last head's share
+    assert _packed(2, 8192, H, D, 64, sa_t=1, sa_h=last)
+    assert not _packed(2, 8192, H, D, 64, sa_t=1, sa_h=last + 1)
+    assert not _packed(2, 8192, H, D, 64, sa_t=1, sa_h=2 ** 29)
+    last = (lim - (pack - 1) * 4) // 64                 # rows of a far apart, heads next to each other
+    assert _packed(1, 16384, H, D, 64, sa_t=last)
+    if last + 1 <= lim // 64:                           # (else refused, as one head's offsets are)
+        assert not _packed(1, 16384, H, D, 64, sa_t=last + 1)
+
+
+@pytest.mark.parametrize("H,D,block", [(3, 16, 16), (4, 16, 128), (5, 32, 32), (2, 32, 64)])
+def test_packed_heads_bound_the_carriers_offsets(H, D, block):
+    blocks = (2 ** 31 - 1) // 256                       # 64 channels of float32 a block
+    assert _packed(1, blocks * block - 1, H, D, block)
+    assert not _packed(1, (blocks + 1) * block, H, D, block)

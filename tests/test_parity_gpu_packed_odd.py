@@ -95,3 +95,36 @@ def test_odd_head_counts_write_only_their_outputs(swr, B, T, H, D, block, dtype)
     for g in (gy, gv) + guards:
         assert all(bool((t == 7.0).all()) for t in g)
     check_full(prob, y, outs, what="packed odd guarded")
+
+
+def _strided_like(t, strides, dtype=None):
+    """t's values in memory of these strides."""
+    r = torch.empty_strided(t.shape, strides, dtype=dtype or t.dtype, device=t.device)
+    return r.copy_(t)
+
+
+@pytest.mark.parametrize("H,D,log2_stride", [(3, 16, 28), (3, 16, 29), (4, 16, 28), (2, 32, 30)])
+def test_decays_of_far_apart_heads(swr, H, D, log2_stride):
+    # a's and da's heads lie 2^31 bytes and more from the first: past a lane's 32-bit offset
+    B, T, block = 2, 8192, 64
+    prob = W.random_problem(185 + H, B, T, H, D, block, "bf16", "sigmoid", 3.0)
+    x, a, b, c, dy = (to_device(getattr(prob, n), "bf16") for n in ("x", "a", "b", "c", "dy"))
+    far = (T, 1, 1 << log2_stride)
+    a = _strided_like(a, far)
+    y, v = swr.swr_forward(x, a, b, c, block, save_carriers=True)
+    outs = [torch.empty_like(x), torch.empty_strided((B, T, H), far, dtype=torch.float32, device="cuda"),
+            torch.empty_like(x), torch.empty_like(x)]
+    outs[1].fill_(float("nan"))
+    for carriers in (v, None):
+        grads = swr.swr_backward(x, a, b, c, dy, carriers, block, outputs=outs)
+        torch.cuda.synchronize()
+        check_full(prob, y, grads, what=f"far heads {H}x{D} 2^{log2_stride}")
+    ye, ve, hl = swr.swr_exact_forward(x, a, b, c, block, save_carriers=True, want_h_last=True)
+    grads = swr.swr_exact_backward(x, a, b, c, dy, ve, block, outputs=outs)
+    torch.cuda.synchronize()
+    ref_y, ref_hl = oracle.exact_forward(prob.x, prob.a, prob.b, prob.c)
+    assert_close(to_host(ye), ref_y, "bf16", "y")
+    assert_close(to_host(hl), ref_hl, "bf16", "h_last")
+    for name, got, ref in zip(("dx", "da", "db", "dc"), grads, oracle.exact_backward(prob.x, prob.a, prob.b, prob.c,
+                                                                                    prob.dy)):
+        assert_close(to_host(got), ref, "bf16", name)
