@@ -184,6 +184,23 @@ int resolve(const swr_problem_t* p, Resolved* r, bool allow_pack = true, bool al
 
     r->es = p->dtype == SWR_DTYPE_BF16 ? 2 : 4;
     r->pc = (p->flags & SWR_FLAG_PER_CHANNEL_DECAY) != 0;
+    // Sizes and strides come first: the plan below multiplies them.
+    r->empty = p->B == 0 || p->T == 0 || p->H == 0;
+    r->xspan = r->aspan = 0;
+    if (!r->empty) {   // strides of an empty tensor are meaningless
+        Dim xd[4] = {{p->B, p->sx_b}, {p->T, p->sx_t}, {p->H, p->sx_h}, {p->D, 1}};
+        const int64_t xo = max_offset(xd, 4);
+        if (xo < 0 || !non_overlapping(xd, 4)) return SWR_ERR_SHAPE;
+        r->xspan = (xo + 1) * r->es;
+        if (r->pc) {       // a and da use the strides of x; sa_* are not read
+            r->aspan = xo + 1;
+        } else {
+            Dim ad[3] = {{p->B, p->sa_b}, {p->T, p->sa_t}, {p->H, p->sa_h}};
+            const int64_t ao = max_offset(ad, 3);
+            if (ao < 0 || !non_overlapping(ad, 3)) return SWR_ERR_SHAPE;
+            r->aspan = ao + 1;
+        }
+    }
     // A head wider than one kernel head is split into 2^hshift virtual heads
     // of dv channels; a virtual head narrower than the kernel's width dk (a
     // power of two) leaves the lanes past nlane idle.
@@ -204,7 +221,7 @@ int resolve(const swr_problem_t* p, Resolved* r, bool allow_pack = true, bool al
     // run length, tuned with the heads one by one, keeps them so.
     if (allow_pack && !r->pc && (p->D == 16 || p->D == 32) && p->sx_h == p->D && packed_offsets_fit(p, 64 / p->D) &&
         (p->H % (64 / p->D) == 0 ||
-         (p->H >= 2 && p->run_len == 0 && (r->es == 2 || allow_pair) && p->B * p->H * p->T >= 32768))) {
+         (p->H >= 2 && !r->empty && p->run_len == 0 && (r->es == 2 || allow_pair) && p->B * p->H * p->T >= 32768))) {
         r->pack = (int)(64 / p->D);
         r->dk = 64;
     }
@@ -232,22 +249,6 @@ int resolve(const swr_problem_t* p, Resolved* r, bool allow_pack = true, bool al
     r->step = (int64_t)std::max(r->bwd.tw, r->fwd.tw) * 16;   // both sweeps' steps divide a run
     if (p->run_len < 0 || (p->run_len > 0 && p->run_len % r->step != 0)) return SWR_ERR_UNSUPPORTED;
 
-    r->empty = p->B == 0 || p->T == 0 || p->H == 0;
-    r->xspan = r->aspan = 0;
-    if (!r->empty) {   // strides of an empty tensor are meaningless
-        Dim xd[4] = {{p->B, p->sx_b}, {p->T, p->sx_t}, {p->H, p->sx_h}, {p->D, 1}};
-        const int64_t xo = max_offset(xd, 4);
-        if (xo < 0 || !non_overlapping(xd, 4)) return SWR_ERR_SHAPE;
-        r->xspan = (xo + 1) * r->es;
-        if (r->pc) {       // a and da use the strides of x; sa_* are not read
-            r->aspan = xo + 1;
-        } else {
-            Dim ad[3] = {{p->B, p->sa_b}, {p->T, p->sa_t}, {p->H, p->sa_h}};
-            const int64_t ao = max_offset(ad, 3);
-            if (ao < 0 || !non_overlapping(ad, 3)) return SWR_ERR_SHAPE;
-            r->aspan = ao + 1;
-        }
-    }
     const int64_t seqs = p->B * r->hv;             // (batch, head) sequences the kernels see
     if (r->fwd.hw > 1 && p->run_len == 0 && !r->empty) {
         // On a problem too small to fill the forward's grid, grouping heads

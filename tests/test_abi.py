@@ -93,6 +93,10 @@ def test_version_mismatch():
     (dict(block=128, run_len=64), E_UNSUP),
     (dict(x_strides=(256 * 4 * 64, 4 * 64, 1)), E_SHAPE),           # heads overlap channels
     (dict(a_strides=(256 * 4, 1, 1)), E_SHAPE),                       # a overlaps itself
+    # sizes whose product passes 2^63 (the sanitized build of these tests sees an overflow)
+    (dict(B=1 << 31, T=1 << 31, H=(1 << 31) + 1, D=16, x_strides=(1, 1, 16), a_strides=(1, 1, 1)), E_SHAPE),
+    (dict(T=2 ** 63 - 1, D=64, x_strides=(1, 1, 64), a_strides=(1, 1, 1)), E_SHAPE),
+    (dict(B=1 << 40, H=1 << 40, D=256, x_strides=(1, 1, 256), a_strides=(1, 1, 1)), E_SHAPE),
 ])
 def test_shape_validation(kw, code):
     p = problem(**kw)
