@@ -509,17 +509,19 @@ int64_t bwd_agg_len(const swr_problem_t* p, const Resolved& r) {
 // the run (D) and the run's decay product (1, or D for a per-channel decay),
 // for the largest of the launches' run counts.  With one decay per head the
 // arrays start past the one-pass chain's two counters, so that the count of
-// waits that gave up reads zero whichever route a call took.
+// waits that gave up reads zero whichever route a call took.  (The static array
+// holds the forward's runs alone: what it accepts does not hang on how the
+// backward is split.)
 struct ExactWs {
     int64_t nr;       // runs per sequence the workspace is laid out for
     int64_t head;     // float32 elements before the arrays
     int64_t floats;   // total float32 elements
 };
 
-ExactWs exact_ws(const swr_problem_t* p, const Resolved& r) {
+ExactWs exact_ws(const swr_problem_t* p, const Resolved& r, bool forward_only = false) {
     ExactWs w;
     const int64_t na = r.empty ? 0 : (p->T + bwd_agg_len(p, r) - 1) / bwd_agg_len(p, r);
-    w.nr = std::max(std::max(r.nruns, r.nruns_f), na);
+    w.nr = forward_only ? r.nruns_f : std::max(std::max(r.nruns, r.nruns_f), na);
     w.head = !r.empty && !r.pc ? 16 : 0;
     // a per-channel decay has one run decay product per channel
     w.floats = w.head + p->B * p->H * w.nr * (2 * p->D + (r.pc || r.pack > 1 ? p->D : 1));
@@ -705,10 +707,10 @@ int swr::exact_forward_impl(const swr_problem_t* p, const void* x, const void* a
     if (!r.natural) return SWR_ERR_UNSUPPORTED;
     // (packed heads of a count that fills no whole virtual head: the chain of
     // the heads one by one may fit the static array where the stages do not)
-    if (scratch && r.pack > 1 && p->H % r.pack && exact_ws(p, r).floats * 4 > scratch_bytes &&
+    if (scratch && r.pack > 1 && p->H % r.pack && exact_ws(p, r, true).floats * 4 > scratch_bytes &&
         (rc = resolve(p, &r, false)) != SWR_OK)
         return rc;
-    ExactWs w = exact_ws(p, r);
+    ExactWs w = exact_ws(p, r, scratch != nullptr);
     // the library's static array may hold the three stages' arrays but not the
     // one pass's: the allocation-free call then runs the three stages.  bf16
     // heads of 64 channels run in pairs where the pointers and strides allow.

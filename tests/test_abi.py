@@ -433,6 +433,22 @@ def test_exact_forward_noalloc_validation():
         assert nfwd(problem(**kw), 0, 0, 0, 0, 0, 0, 0, 0) == OK
 
 
+@reaches_launch
+@pytest.mark.parametrize("B,T,H,D,block,dtype,per_channel", [
+    (1, 978811, 16, 128, 64, BF16, True),     # 4 GB a tensor
+    (4, 737280, 7, 64, 16, F32, True),
+    (16, 583738, 2, 64, 32, BF16, True),
+    (8, 587840, 16, 64, 64, F32, False),
+    (4, 1 << 20, 33, 16, 64, BF16, True),
+])
+def test_noalloc_takes_long_sequences(B, T, H, D, block, dtype, per_channel):
+    # the forward's runs alone (about 512 workgroups) decide what the static
+    # array holds, however finely a long sequence's backward is split
+    p = problem(B=B, T=T, H=H, D=D, block=block, dtype=dtype, per_channel=per_channel)
+    far = [(1 << 44) + (i << 40) for i in range(8)]
+    assert nfwd(p, *far) in (OK, E_HIP)
+
+
 # ----------------------------------------------------------------------------- recurrent decoding
 
 ST = GB * 30
