@@ -48,8 +48,10 @@ struct Sweep {
 };
 int64_t plan_run_len(int64_t T, int64_t units, int64_t step, int64_t halo, const Sweep& s) {
     const int64_t nsteps = (T + step - 1) / step;
-    if (s.len > 0 && units * T / s.len >= 2 * s.cap) {   // whole rounds here too
-        const int64_t r = std::max<int64_t>(1, std::min(nsteps, units * T / s.len / s.cap * s.cap / units));
+    if (s.len > 0 && units * T / s.len >= 2 * s.cap) {
+        // (no more workgroups than a launch takes, however long the sequences)
+        const int64_t most = std::min(nsteps, kMaxWorkgroups / 4 / units);
+        const int64_t r = std::max<int64_t>(1, std::min(most, units * T / s.len / s.cap * s.cap / units));
         return (nsteps + r - 1) / r * step;
     }
     int64_t best = nsteps, cost = -1;

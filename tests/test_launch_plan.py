@@ -68,3 +68,19 @@ def test_packed_heads_bound_the_carriers_offsets(H, D, block):
     blocks = (2 ** 31 - 1) // 256                       # 64 channels of float32 a block
     assert _packed(1, blocks * block - 1, H, D, block)
     assert not _packed(1, (blocks + 1) * block, H, D, block)
+
+
+@pytest.mark.parametrize("B,T,H,D,block,dtype,per_channel", [
+    (64, 1670942336, 12, 16, 64, swr.SWR_DTYPE_BF16, False),
+    (64, 686221184, 33, 32, 64, swr.SWR_DTYPE_F32, True),
+    (64, 78976637, 128, 112, 32, swr.SWR_DTYPE_BF16, True),
+])
+def test_short_runs_of_very_long_sequences_fit_a_launch(B, T, H, D, block, dtype, per_channel):
+    # runs of 256 tokens would make more workgroups than a launch takes
+    xs = (T * H * D, D, T * D)
+    p = swr.make_problem(B, T, H, D, block, dtype, xs, xs if per_channel else (T * H, 1, T), per_channel=per_channel)
+    plans = [swr.swr_launch_info(p)] if per_channel else [swr.swr_launch_info(p), swr.swr_uniform_launch_info(p)]
+    for i in plans:
+        assert 0 < i["fwd_workgroups"] < 2 ** 31 and 0 < i["bwd_workgroups"] < 2 ** 31
+    if D != 112:
+        assert swr.swr_exact_workspace_bytes(p) > 0
