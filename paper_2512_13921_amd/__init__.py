@@ -19,6 +19,7 @@ returns gradients with respect to those logits.  Supported dtypes: float32 and
 bfloat16.  The block carriers that the forward saves for the backward are a
 float32 ``[B, H, ceil(T / block), D]`` tensor (``carrier_shape``).
 """
+import contextlib
 import ctypes
 import os
 
@@ -269,6 +270,18 @@ def _stream(stream, device):
     return ctypes.c_void_p(s.cuda_stream)
 
 
+def _on(stream, device):
+    """Context in which tensors are allocated and filled on a call's stream
+    (None: the current one).  What only the call's kernels use, and what they
+    find filled, has to be that stream's: it is let go when the call returns,
+    and nothing else orders it with the kernels."""
+    torch = _torch()
+    if stream is None:
+        return contextlib.nullcontext()
+    raw = stream.cuda_stream
+    return torch.cuda.stream(torch.cuda.ExternalStream(raw, device) if raw else torch.cuda.default_stream(device))
+
+
 def _ptr(t):
     return ctypes.c_void_p(t.data_ptr())
 
@@ -373,11 +386,12 @@ def swr_exact_workspace_bytes(problem: SwrProblem) -> int:
     return n
 
 
-def _workspace(problem, device, workspace):
+def _workspace(problem, device, workspace, stream):
     torch = _torch()
     nbytes = swr_exact_workspace_bytes(problem)
     if workspace is None:
-        return torch.empty(max(nbytes // 4, 1), dtype=torch.float32, device=device)
+        with _on(stream, device):
+            return torch.empty(max(nbytes // 4, 1), dtype=torch.float32, device=device)
     if (workspace.numel() * workspace.element_size() < nbytes or not workspace.is_contiguous()
             or workspace.device != device):
         raise ValueError(f"workspace must be a contiguous tensor of at least {nbytes} bytes on x's device")
@@ -428,7 +442,7 @@ def _exact_forward(noalloc, x, a, b, c, block, h0, residual, y, carriers, save_c
         rc = load().swr_exact_forward_noalloc(ctypes.byref(problem), _ptr(x), _ptr(a), _ptr(b), _ptr(c),
                                               _opt(h0), _ptr(y), _opt(v), _opt(hl), _stream(stream, x.device))
     else:
-        ws = _workspace(problem, x.device, workspace)
+        ws = _workspace(problem, x.device, workspace, stream)
         rc = load().swr_exact_forward(ctypes.byref(problem), _ptr(x), _ptr(a), _ptr(b), _ptr(c), _opt(h0),
                                       _ptr(y), _opt(v), _opt(hl), _ptr(ws), _stream(stream, x.device))
     if rc != 0:
@@ -490,7 +504,7 @@ def swr_exact_backward(x, a, b, c, dy, carriers, block, h0=None, dh_last=None, r
         _da_check(da, a)
     B, T, H, D = x.shape
     dh0 = torch.empty((B, H, D), dtype=torch.float32, device=x.device) if want_dh0 else None
-    ws = _workspace(problem, x.device, workspace)
+    ws = _workspace(problem, x.device, workspace, stream)
     rc = load().swr_exact_backward(ctypes.byref(problem), _ptr(x), _ptr(a), _ptr(b), _ptr(c), _ptr(dy),
                                    _opt(h0), _ptr(carriers), _opt(dh_last), _ptr(dx), _ptr(da), _ptr(db),
                                    _ptr(dc), _opt(dh0), _ptr(ws), _stream(stream, x.device))
@@ -666,7 +680,8 @@ def swr_backward_shared_gates(x, a, b, c, dy, carriers, block, group, residual=F
         _da_check(da, a)
     nbytes = swr_shared_gates_workspace_bytes(problem, group)
     if workspace is None:
-        workspace = torch.empty(nbytes // 4, dtype=torch.float32, device=x.device) if nbytes else None
+        with _on(stream, x.device):
+            workspace = torch.empty(nbytes // 4, dtype=torch.float32, device=x.device) if nbytes else None
     elif (workspace.numel() * workspace.element_size() < nbytes or not workspace.is_contiguous()
           or workspace.device != x.device):
         raise ValueError(f"workspace must be a contiguous tensor of at least {nbytes} bytes on x's device")

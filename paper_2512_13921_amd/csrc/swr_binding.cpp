@@ -143,6 +143,23 @@ void* stream_of(PyObject* o, const at::Tensor& x, bool* ok) {
     return PyLong_AsVoidPtr(o);
 }
 
+// n floats that only one call's kernels use, on its stream (o, st: the stream
+// argument and its address).  The tensor is let go when the call returns, so
+// it is taken from that stream's memory: whoever gets it next is ordered
+// behind those kernels there, and it has no other stream's work pending.
+at::Tensor workspace(const at::Tensor& x, int64_t n, PyObject* o, void* st) {
+    if (o == Py_None) return floats(x, {n});
+    struct On {
+        const c10::hip::HIPStream before;
+        On(c10::DeviceIndex d, void* s) : before(c10::hip::getCurrentHIPStream(d)) {
+            c10::hip::setCurrentHIPStream(s ? c10::hip::getStreamFromExternal((hipStream_t)s, d)
+                                            : c10::hip::getDefaultHIPStream(d));
+        }
+        ~On() { c10::hip::setCurrentHIPStream(before); }
+    } on(x.device().index(), st);
+    return floats(x, {n});
+}
+
 PyObject* none() { Py_RETURN_NONE; }
 
 PyObject* results(int rc, std::initializer_list<at::Tensor> ts) {
@@ -228,7 +245,7 @@ PyObject* exact_forward(PyObject*, PyObject* const* v, Py_ssize_t) {
     at::Tensor s, hl;
     if (want_v) s = floats(in.x, carrier_shape(p));
     if (want_h) hl = floats(in.x, hs);
-    const at::Tensor work = floats(in.x, {std::max<int64_t>(ws / 4, 1)});
+    const at::Tensor work = workspace(in.x, std::max<int64_t>(ws / 4, 1), *g.v, st);
     return results(call(abi.fn.exact_forward, &p, ptr(in.x), ptr(in.a), ptr(in.b), ptr(in.c), fptr(h0), ptr(y), fptr(s),
                                         fptr(hl), ptr(work), st), {y, s, hl});
     END_HANDLE_TH_ERRORS
@@ -256,7 +273,7 @@ PyObject* exact_backward(PyObject*, PyObject* const* v, Py_ssize_t) {
     const at::Tensor dx = like(in.x), db = like(in.x), dc = like(in.x), da = decay_gradient(in.a);
     at::Tensor dh0;
     if (want) dh0 = floats(in.x, hs);
-    const at::Tensor work = floats(in.x, {std::max<int64_t>(ws / 4, 1)});
+    const at::Tensor work = workspace(in.x, std::max<int64_t>(ws / 4, 1), *g.v, st);
     return results(call(abi.fn.exact_backward, &p, ptr(in.x), ptr(in.a), ptr(in.b), ptr(in.c), ptr(dy), fptr(h0),
                           fptr(s),
                                          fptr(dhl), ptr(dx), fptr(da), ptr(db), ptr(dc), fptr(dh0), ptr(work), st),
@@ -380,7 +397,7 @@ PyObject* backward_shared_gates(PyObject*, PyObject* const* v, Py_ssize_t) {
     if (ws < 0) return none();
     const at::Tensor dx = like(in.x), db = like(in.b), dc = like(in.b), da = decay_gradient(in.a);
     at::Tensor work;
-    if (ws > 0) work = floats(in.x, {ws / 4});
+    if (ws > 0) work = workspace(in.x, ws / 4, *g.v, st);
     return results(call(abi.fn.backward_shared_gates, &p, group, in.b.strides().data(), ptr(in.x), ptr(in.a), ptr(in.b),
                                                 ptr(in.c), ptr(dy), fptr(s), ptr(dx), fptr(da), ptr(db), ptr(dc),
                                                 ptr(work), st), {dx, da, db, dc});

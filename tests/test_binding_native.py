@@ -119,3 +119,50 @@ def test_stream_argument_and_current_stream(swr):
         y2 = swr.swr_forward(x, a, b, c, 32)
     torch.cuda.synchronize()
     assert torch.equal(y1, ref) and torch.equal(y2, ref)
+
+
+def _workspace_calls(swr):
+    """The calls that allocate a workspace of their own, as functions of the stream."""
+    x, a, b, c, dy, _, _ = _inputs(torch.bfloat16, T=700, H=32)
+    gb, gc = b[:, :, :1].contiguous(), c[:, :, :1].contiguous()   # one gate for 32 heads: summed in a workspace
+    _, ve = swr.swr_exact_forward(x, a, b, c, 32, save_carriers=True)
+    _, vg = swr.swr_forward_shared_gates(x, a, gb, gc, 32, 32, save_carriers=True)
+    return (lambda s: swr.swr_exact_forward(x, a, b, c, 32, save_carriers=True, want_h_last=True, stream=s),
+            lambda s: swr.swr_exact_backward(x, a, b, c, dy, ve, 32, want_dh0=True, stream=s),
+            lambda s: swr.swr_backward_shared_gates(x, a, gb, gc, dy, vg, 32, 32, stream=s))
+
+
+@pytest.mark.parametrize("native", [True, False])
+@pytest.mark.parametrize("call", range(3))
+def test_a_call_s_own_workspace_is_its_stream_s(swr, monkeypatch, native, call):
+    # The caller never sees the workspace, so nothing it does can keep the next
+    # allocation off it: it has to be memory of the stream the kernels run on.
+    if not native:
+        monkeypatch.setattr(swr, "_native", (swr._lib, _Nothing()))
+    run = _workspace_calls(swr)[call]
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    s = torch.cuda.Stream()
+    before = {m["address"] for m in torch.cuda.memory_snapshot()}
+    run(s)
+    torch.cuda.synchronize()
+    assert any(m["stream"] == s.cuda_stream and m["address"] not in before for m in torch.cuda.memory_snapshot())
+
+
+@pytest.mark.parametrize("native", [True, False])
+def test_calls_on_another_stream_among_allocations_here(swr, monkeypatch, native):
+    if not native:
+        monkeypatch.setattr(swr, "_native", (swr._lib, _Nothing()))
+    calls = _workspace_calls(swr)
+    refs = [run(None) for run in calls]
+    torch.cuda.synchronize()
+    s = torch.cuda.Stream()
+    for run, ref in zip(calls, refs):
+        with torch.cuda.stream(s):
+            torch.cuda._sleep(20_000_000)
+        outs = run(s)
+        filled = [torch.full((n,), float("nan"), device="cuda") for n in (1 << 10, 1 << 14, 1 << 18, 1 << 20, 1 << 22)]
+        torch.cuda.synchronize()
+        for u, w in zip(outs, ref):
+            assert torch.equal(u, w)
+        del filled
