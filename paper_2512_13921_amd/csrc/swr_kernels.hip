@@ -886,6 +886,10 @@ __global__ __launch_bounds__(TW * 64, 2) void swr_bwd_agg_kernel(Params p) {
 // segment is one batch of loads, else read again, from L2).  One thread per
 // channel over all runs, eight loads ahead, took 152 us for 1096 runs
 // (6 sequences of packed 64-channel heads), this 11; for 508 runs 74, 7.
+//
+// Decays above 1 can take a segment's product or its state from zero past
+// float32's range where the chain itself stays inside (a state of zero stays
+// zero): such a segment is walked run by run instead.
 constexpr int kScanBatch = 8;      // aggregates a thread loads at a time
 constexpr int64_t kScanShort = 16 * kScanBatch;   // runs that 16 segments hold in registers
 
@@ -925,7 +929,17 @@ __global__ __launch_bounds__(SEGS * 16) void swr_scan_kernel(ScanParams q) {
         __syncthreads();
         float S = q.init ? q.init[seq * q.D + ch] : 0.0f;
         const int last = q.nruns > 0 ? (int)((q.nruns - 1) / len) : 0;   // the last segment with runs
-        for (int s = 0; s < min(sg, last); ++s) S = __builtin_fmaf(s_P[s][c], S, s_V[s][c]);
+        for (int s = 0; s < min(sg, last); ++s) {
+            const float Ps = s_P[s][c], Vs = s_V[s][c];
+            if (__builtin_isfinite(Ps) && __builtin_isfinite(Vs)) {
+                S = __builtin_fmaf(Ps, S, Vs);
+            } else {
+                for (int64_t j = s * len; j < (s + 1) * len; ++j) {   // (s < last: a whole segment)
+                    const int64_t r = q.reverse ? q.nruns - 1 - j : j;
+                    S = __builtin_fmaf(pp[r * pstride], S, v[r * q.D]);
+                }
+            }
+        }
         for (int64_t j0 = lo; j0 < hi; j0 += kScanBatch) {
             if (len > kScanBatch) load(j0);
 #pragma unroll
