@@ -1139,71 +1139,72 @@ template <class IO, int CPL, bool PC, bool FEAT>
 __global__ __launch_bounds__(256) void swr_state_kernel(StateParams q) {
     constexpr int D = CPL * SB;
     constexpr int ES = IO::ES;
-    const int64_t seq = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (seq >= q.B * q.H) return;   // whole waves leave; no barriers below
     const int sig_a = FEAT ? q.sig_a : 0;
     const int lane = threadIdx.x & 63, grp = lane >> 4, n = lane & 15;
-    const int64_t bb = seq / q.H, hh = seq - bb * q.H;
-    float e[CPL], s[CPL];
+    // (a launch holds fewer than 2^32 threads: waves take further sequences past its grid)
+    for (int64_t seq = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); seq < q.B * q.H; seq += (int64_t)gridDim.x * 4) {
+        const int64_t bb = seq / q.H, hh = seq - bb * q.H;
+        float e[CPL], s[CPL];
 #pragma unroll
-    for (int m = 0; m < CPL; ++m) { e[m] = 0.f; s[m] = 0.f; }
-    if (q.T > 0) {
-        const int64_t tau = (q.T - 1) >> q.lshift, t_blk = tau << q.lshift;
-        const int cnt = (int)(q.T - t_blk);   // tokens of the last block, 1 .. 128
-        const float* vb = q.carriers + seq * q.nblocks * D + n * CPL;
-        Row<IoF32, CPL> rv, rp;
-        gload(rv, vb + tau * D);
-        if (tau > 0)
-            gload(rp, vb + (tau - 1) * D);
-        else
-            rp.zero();
-        const int64_t as = q.sa_t * ES;
-        const char* ab = (const char*)q.a + (bb * q.sa_b + hh * q.sa_h) * ES + t_blk * as;
-        float G[CPL];
-        if constexpr (PC) {   // lane group g: tokens g, g + 4, ...
+        for (int m = 0; m < CPL; ++m) { e[m] = 0.f; s[m] = 0.f; }
+        if (q.T > 0) {
+            const int64_t tau = (q.T - 1) >> q.lshift, t_blk = tau << q.lshift;
+            const int cnt = (int)(q.T - t_blk);   // tokens of the last block, 1 .. 128
+            const float* vb = q.carriers + seq * q.nblocks * D + n * CPL;
+            Row<IoF32, CPL> rv, rp;
+            gload(rv, vb + tau * D);
+            if (tau > 0)
+                gload(rp, vb + (tau - 1) * D);
+            else
+                rp.zero();
+            const int64_t as = q.sa_t * ES;
+            const char* ab = (const char*)q.a + (bb * q.sa_b + hh * q.sa_h) * ES + t_blk * as;
+            float G[CPL];
+            if constexpr (PC) {   // lane group g: tokens g, g + 4, ...
 #pragma unroll
-            for (int m = 0; m < CPL; ++m) G[m] = 1.f;
-            for (int i0 = 0; i0 < cnt; i0 += 32) {
-                Row<IO, CPL> ar[8];
+                for (int m = 0; m < CPL; ++m) G[m] = 1.f;
+                for (int i0 = 0; i0 < cnt; i0 += 32) {
+                    Row<IO, CPL> ar[8];
 #pragma unroll
-                for (int i = 0; i < 8; ++i)   // (past the end: the last row again, not multiplied)
-                    gload(ar[i], ab + min(i0 + 4 * i + grp, cnt - 1) * as + n * CPL * ES);
+                    for (int i = 0; i < 8; ++i)   // (past the end: the last row again, not multiplied)
+                        gload(ar[i], ab + min(i0 + 4 * i + grp, cnt - 1) * as + n * CPL * ES);
 #pragma unroll
-                for (int i = 0; i < 8; ++i)
+                    for (int i = 0; i < 8; ++i)
 #pragma unroll
-                    for (int m = 0; m < CPL; ++m) {
-                        const float z = ar[i].get(m);
-                        G[m] *= i0 + 4 * i + grp < cnt ? (sig_a ? sigmoid(z) : z) : 1.0f;
-                    }
+                        for (int m = 0; m < CPL; ++m) {
+                            const float z = ar[i].get(m);
+                            G[m] *= i0 + 4 * i + grp < cnt ? (sig_a ? sigmoid(z) : z) : 1.0f;
+                        }
+                }
+#pragma unroll
+                for (int m = 0; m < CPL; ++m) {
+                    G[m] *= __shfl_xor(G[m], 16, 64);
+                    G[m] *= __shfl_xor(G[m], 32, 64);
+                }
+            } else {   // lane i: tokens i and i + 64
+                float g = 1.f;
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    const int t = lane + 64 * i;
+                    const float z = gload_scalar<IO>(ab + min(t, cnt - 1) * as);
+                    g *= t < cnt ? (sig_a ? sigmoid(z) : z) : 1.0f;
+                }
+#pragma unroll
+                for (int w = 1; w < 64; w <<= 1) g *= __shfl_xor(g, w, 64);
+#pragma unroll
+                for (int m = 0; m < CPL; ++m) G[m] = g;
             }
 #pragma unroll
             for (int m = 0; m < CPL; ++m) {
-                G[m] *= __shfl_xor(G[m], 16, 64);
-                G[m] *= __shfl_xor(G[m], 32, 64);
+                s[m] = rv.get(m);
+                e[m] = s[m] + G[m] * rp.get(m);
             }
-        } else {   // lane i: tokens i and i + 64
-            float g = 1.f;
-#pragma unroll
-            for (int i = 0; i < 2; ++i) {
-                const int t = lane + 64 * i;
-                const float z = gload_scalar<IO>(ab + min(t, cnt - 1) * as);
-                g *= t < cnt ? (sig_a ? sigmoid(z) : z) : 1.0f;
-            }
-#pragma unroll
-            for (int w = 1; w < 64; w <<= 1) g *= __shfl_xor(g, w, 64);
-#pragma unroll
-            for (int m = 0; m < CPL; ++m) G[m] = g;
         }
-#pragma unroll
-        for (int m = 0; m < CPL; ++m) {
-            s[m] = rv.get(m);
-            e[m] = s[m] + G[m] * rp.get(m);
+        if (grp == 0) {
+            float* st = q.state + seq * 2 * D + n * CPL;
+            gstore<IoF32, CPL>(st, e);
+            gstore<IoF32, CPL>(st + D, s);
         }
-    }
-    if (grp == 0) {
-        float* st = q.state + seq * 2 * D + n * CPL;
-        gstore<IoF32, CPL>(st, e);
-        gstore<IoF32, CPL>(st + D, s);
     }
 }
 
@@ -2069,7 +2070,8 @@ hipError_t launch_step(const StepParams& q, int dtype, int D, bool exact, bool p
 
 template <class IO, int CPL>
 static hipError_t launch_state_cpl(const StateParams& q, bool pc, hipStream_t st) {
-    const dim3 grid((unsigned)((q.B * q.H + 3) / 4)), blk(256);   // a wave per sequence
+    // a wave per sequence, of a grid that a launch takes
+    const dim3 grid((unsigned)std::min<int64_t>((q.B * q.H + 3) / 4, 1 << 20)), blk(256);
     const int sel = (pc ? 2 : 0) | (q.sig_a ? 1 : 0);
     switch (sel) {
         case 0: hipLaunchKernelGGL((swr_state_kernel<IO, CPL, false, false>), grid, blk, 0, st, q); break;

@@ -24,3 +24,16 @@ def test_decode_state_last_block_lengths(last, D, dtype, per_channel, logits):
     torch.cuda.synchronize()
     _, ref = oracle.step(prob.x, prob.a, prob.b, prob.c, None, 0, 128, sigmoid_decay=logits)
     assert_close(to_host(st), ref, dtype, f"decode state, last block of {last}")
+
+
+def test_decode_state_of_more_sequences_than_a_grid_of_waves():
+    # 2^26 waves would be 2^32 threads, more than a launch takes
+    import paper_2512_13921_amd as swr
+    B, H, D = 4099, 16384, 16
+    x = torch.empty((B, 1, H, D), dtype=torch.bfloat16, device="cuda")
+    a = torch.full((B, 1, H), 0.5, dtype=torch.bfloat16, device="cuda")
+    v = torch.rand((B, H, 1, D), device="cuda")
+    st = swr.swr_decode_state(x, a, v, 16)
+    torch.cuda.synchronize()
+    # one token: both states are the first block's carrier
+    assert torch.equal(st[:, :, 0], v[:, :, 0]) and torch.equal(st[:, :, 1], v[:, :, 0])
