@@ -516,12 +516,14 @@ def swr_exact_backward(x, a, b, c, dy, carriers, block, h0=None, dh_last=None, r
 # ----------------------------------------------------------------------------- recurrent decoding
 
 
-def _step_state(state, x, exact):
+def _step_state(state, x, exact, stream=None):
     torch = _torch()
     B, K, H, D = x.shape
     shape = (B, H, D) if exact else (B, H, 2, D)
     if state is None:
-        return torch.zeros(shape, dtype=torch.float32, device=x.device)
+        state = torch.empty(shape, dtype=torch.float32, device=x.device)
+        with _on(stream, x.device):
+            return state.zero_()
     if (tuple(state.shape) != shape or state.dtype != torch.float32 or not state.is_contiguous()
             or state.device != x.device):
         raise ValueError(f"state must be a contiguous float32 tensor of shape {shape}")
@@ -541,7 +543,7 @@ def swr_step(x, a, b, c, block, t0, state=None, residual=False, y=None, stream=N
     torch = _torch()
     problem = _problem_from(x, a, block, residual, 0, sigmoid_decay, sigmoid_pregate)
     _same_layout(x, b, c)
-    state = _step_state(state, x, False)
+    state = _step_state(state, x, False, stream)
     if y is None:
         y = torch.empty_strided(x.shape, x.stride(), dtype=x.dtype, device=x.device)
     else:
@@ -564,7 +566,7 @@ def swr_exact_step(x, a, b, c, state=None, residual=False, y=None, stream=None,
     torch = _torch()
     problem = _problem_from(x, a, 16, residual, 0, sigmoid_decay, sigmoid_pregate)
     _same_layout(x, b, c)
-    state = _step_state(state, x, True)
+    state = _step_state(state, x, True, stream)
     if y is None:
         y = torch.empty_strided(x.shape, x.stride(), dtype=x.dtype, device=x.device)
     else:

@@ -166,3 +166,22 @@ def test_calls_on_another_stream_among_allocations_here(swr, monkeypatch, native
         for u, w in zip(outs, ref):
             assert torch.equal(u, w)
         del filled
+
+
+def test_a_state_of_zeros_is_filled_on_the_call_s_stream(swr):
+    # the current stream is still busy when the step on another stream reads its state
+    x, a, b, c, *_ = _inputs(torch.bfloat16, T=2)
+    steps = (lambda s: swr.swr_step(x, a, b, c, 32, 0, stream=s), lambda s: swr.swr_exact_step(x, a, b, c, stream=s))
+    for step in steps:
+        y, st = step(None)
+        torch.cuda.synchronize()
+        unlike = torch.full_like(st, 7.0)   # what the next state's memory holds
+        torch.cuda.synchronize()
+        del unlike
+        s = torch.cuda.Stream()
+        torch.cuda._sleep(200_000_000)
+        y2, st2 = step(s)
+        with torch.cuda.stream(s):
+            same = torch.equal(y2, y) and torch.equal(st2, st)
+        torch.cuda.synchronize()
+        assert same
