@@ -5,9 +5,9 @@ arguments) and only marshal torch tensors into pointers, strides and the
 current HIP stream; every step of the computation runs in the library's HIP
 kernels.  The ordinary call (plain GPU tensors that pass every check, outputs
 allocated here) is marshalled in native code (``csrc/swr_binding.cpp``); the
-Python code below takes the others and raises what there is to raise.  There
-is no CPU fallback: without the built library, or without a
-GPU, the calls raise.
+Python code below takes the others, and all of them where that module cannot
+be built or loaded, and raises what there is to raise.  There is no CPU
+fallback: without the built library, or without a GPU, the calls raise.
 
 Layouts: ``x, b, c, y, dy, dx, db, dc`` are ``[B, T, H, D]`` (channels
 contiguous, all with the same strides); ``a`` is ``[B, T, H]`` in the same
@@ -21,7 +21,9 @@ float32 ``[B, H, ceil(T / block), D]`` tensor (``carrier_shape``).
 """
 import contextlib
 import ctypes
+import importlib.util
 import os
+import warnings
 
 from . import build as _build
 
@@ -131,7 +133,30 @@ def load():
 _BOUND = ("swr_forward", "swr_backward", "swr_exact_workspace_bytes", "swr_exact_forward", "swr_exact_backward",
           "swr_step", "swr_exact_step", "swr_decode_state", "swr_uniform_forward", "swr_uniform_backward",
           "swr_forward_shared_gates", "swr_backward_shared_gates", "swr_shared_gates_workspace_bytes")
-_native = None   # (the library it is bound to, the extension module)
+_native = None   # (the library it is bound to, the extension module or what stands for it)
+
+
+class _PythonOnly:
+    """Stands for the native marshalling where there is none: it takes no call."""
+
+    def __getattr__(self, name):
+        return lambda *args: None
+
+
+def _load_binding():
+    """The native marshalling's extension module, built first where it is
+    missing or of another source, C ABI, Python or torch.  Without it every
+    call still runs, marshalled in Python."""
+    try:
+        if not _build.binding_is_current():
+            _build.build_binding()
+        spec = importlib.util.spec_from_file_location(f"{__name__}._binding", _build.BINDING)
+        module = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(module)
+        return module
+    except Exception as e:   # (no compiler, no headers, a read-only package, a module that does not load)
+        warnings.warn(f"calls are marshalled in Python, which costs small ones about 10 us each: {e}", RuntimeWarning)
+        return None
 
 
 def _fast():
@@ -139,12 +164,10 @@ def _fast():
     global _native
     lib = _lib or load()
     if _native is None or _native[0] is not lib:
-        if not os.path.exists(_build.BINDING):
-            _build.build_binding()
-        _torch()
-        from . import _binding
-        _binding.bind(*(ctypes.cast(getattr(lib, n), ctypes.c_void_p).value for n in _BOUND))
-        _native = (lib, _binding)
+        module = _load_binding()
+        if module is not None:
+            module.bind(*(ctypes.cast(getattr(lib, n), ctypes.c_void_p).value for n in _BOUND))
+        _native = (lib, module or _PythonOnly())
     return _native[1]
 
 

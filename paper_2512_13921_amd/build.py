@@ -4,6 +4,7 @@ native marshalling of its Python binding, ``paper_2512_13921_amd/_binding.so``.
 Usage: ``python -m paper_2512_13921_amd.build`` (or ``python paper_2512_13921_amd/build.py``).
 Cross-compiles on a machine without a GPU.
 """
+import hashlib
 import os
 import re
 import shutil
@@ -16,11 +17,11 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libswr.so")
 BINDING = os.path.join(HERE, "_binding.so")
 BINDING_SOURCE = os.path.join(CSRC, "swr_binding.cpp")
+ABI_HEADER = os.path.join(os.path.dirname(HERE), "include", "swr.h")
 SOURCES = [os.path.join(CSRC, n) for n in ("swr_api.cpp", "swr_kernels.hip", "swr_uniform.hip", "swr_groups.hip",
                                             "swr_noalloc.hip", "swr_chain.hip")]
 HEADERS = [os.path.join(CSRC, "swr_launch.h"), os.path.join(CSRC, "swr_device.h"),
-           os.path.join(CSRC, "swr_internal.h"),
-           os.path.join(os.path.dirname(HERE), "include", "swr.h")]
+           os.path.join(CSRC, "swr_internal.h"), ABI_HEADER]
 ARCH = "gfx950"
 
 
@@ -80,12 +81,37 @@ def _messages(res) -> list:
             if not any(n in ln for n in noise) and not quoted.match(ln)]
 
 
+def _temporary(out: str) -> str:
+    """A name next to ``out`` that no other process builds to."""
+    return f"{out}.tmp{os.getpid():x}"
+
+
+def binding_key() -> str:
+    """What the binding's extension module depends on: its source, the C ABI,
+    and the Python and torch that it is compiled against."""
+    import torch
+    key = hashlib.sha256(f"{sys.version} {torch.__version__}".encode())
+    for path in (BINDING_SOURCE, ABI_HEADER):
+        with open(path, "rb") as f:
+            key.update(f.read())
+    return key.hexdigest()
+
+
+def binding_is_current() -> bool:
+    """Whether the built extension module carries today's key."""
+    if not os.path.exists(BINDING):
+        return False
+    with open(BINDING, "rb") as f:
+        return f"swr-binding-key:{binding_key()}".encode() in f.read()
+
+
 def binding_command(out: str) -> list:
     """The host compiler's line for the binding's extension module."""
     import sysconfig
     from torch.utils import cpp_extension
     lib = cpp_extension.library_paths()[0]
     return ["g++", "-std=c++17", "-O2", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+            f'-DSWR_BINDING_KEY="{binding_key()}"',
             *(f"-isystem{p}" for p in (*cpp_extension.include_paths(), "/opt/rocm/include",
                                        sysconfig.get_paths()["include"])),
             BINDING_SOURCE, f"-L{lib}", f"-Wl,-rpath,{lib}", "-ltorch_python", "-ltorch", "-ltorch_cpu", "-lc10",
@@ -93,19 +119,19 @@ def binding_command(out: str) -> list:
 
 
 def build_binding(verbose: bool = False) -> str:
-    cmd = binding_command(BINDING + ".tmp")
+    tmp = _temporary(BINDING)
+    cmd = binding_command(tmp)
     if verbose:
         print(" ".join(cmd))
     res = subprocess.run(cmd, capture_output=True, text=True)
     if res.returncode != 0:
         raise RuntimeError("g++ failed on the binding:\n" + res.stdout + res.stderr)
-    os.replace(BINDING + ".tmp", BINDING)
+    os.replace(tmp, BINDING)
     return BINDING
 
 
 def build(verbose: bool = False, extra=(), out: str = LIB) -> str:
-    """Compiles every source to an object (in parallel), then links ``out``
-    (and, with the library in its place, builds the binding's extension)."""
+    """Compiles every source to an object (in parallel), then links ``out``."""
     with tempfile.TemporaryDirectory() as tmp:
         objs = [os.path.join(tmp, os.path.basename(s) + ".o") for s in SOURCES]
         procs = []
@@ -128,15 +154,13 @@ def build(verbose: bool = False, extra=(), out: str = LIB) -> str:
                 failed.append("kernels that must not spill registers do:\n  " + "\n  ".join(spills))
         if failed:
             raise RuntimeError("hipcc failed:\n" + "\n".join(failed))
-        cmd = link_command(objs, out + ".tmp")
+        cmd = link_command(objs, _temporary(out))
         if verbose:
             print(" ".join(cmd))
         res = subprocess.run(cmd, capture_output=True, text=True)
         if res.returncode != 0:
             raise RuntimeError("hipcc link failed:\n" + "\n".join(_messages(res)))
-    os.replace(out + ".tmp", out)
-    if out == LIB:
-        build_binding(verbose)
+    os.replace(_temporary(out), out)
     return out
 
 
@@ -149,3 +173,4 @@ def is_stale() -> bool:
 
 if __name__ == "__main__":
     print(build(verbose=True))
+    print(build_binding(verbose=True))

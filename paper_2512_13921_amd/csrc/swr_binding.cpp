@@ -6,7 +6,8 @@
 // problem of a few MB.  Each function here takes one entry point's arguments in
 // a fixed order and handles the ordinary call: plain strided GPU tensors that
 // pass every check.  It returns None for anything else, and the caller then
-// runs the Python path, which raises what there is to raise; a status of the C
+// runs the Python path, which raises what there is to raise and which serves
+// every call where this module cannot be built or loaded; a status of the C
 // ABI comes back as an int.  Nothing is kept between calls: the C ABI's entry
 // points are the only state, bound when the library is loaded.
 #define PY_SSIZE_T_CLEAN
@@ -18,6 +19,9 @@
 #include <torch/csrc/autograd/python_variable.h>
 
 #include "../../include/swr.h"
+
+// What this module was built from and for; the build looks for it in the file.
+extern "C" __attribute__((used)) const char swr_binding_key[] = "swr-binding-key:" SWR_BINDING_KEY;
 
 namespace {
 
