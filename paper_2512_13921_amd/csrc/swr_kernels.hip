@@ -893,6 +893,42 @@ __global__ __launch_bounds__(TW * 64, 2) void swr_bwd_agg_kernel(Params p) {
 constexpr int kScanBatch = 8;      // aggregates a thread loads at a time
 constexpr int64_t kScanShort = 16 * kScanBatch;   // runs that 16 segments hold in registers
 
+// Few runs, one batch of loads: one thread per (sequence, channel) walks them
+// all, without the segments' two passes over LDS.  The loads are unconditional
+// (past the end the last run's again, which counts as none), so that all of
+// them are in flight at once (8 runs of 8 sequences of 128 channels: 2.7 us,
+// in 16 segments 3.7; with each load behind its own test 3.7).
+__global__ __launch_bounds__(256) void swr_scan_short_kernel(ScanParams q) {
+    const int shift = 31 - __builtin_clz(q.D);   // D is a power of two
+    const int n = (int)q.nruns;
+    const int64_t ps = q.p_per_channel ? q.D : 1, step = q.reverse ? -1 : 1;
+    for (int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x; idx < q.seqs << shift; idx += (int64_t)gridDim.x * 256) {
+        const int64_t seq = idx >> shift, ch = idx & (q.D - 1);
+        const int64_t r0 = seq * n + (q.reverse ? n - 1 : 0);   // the chain's first run
+        float S = q.init ? q.init[idx] : 0.0f;
+        if (n > 0) {
+            const float* v = q.agg_v + r0 * q.D + ch;
+            const float* pp = q.agg_p + r0 * ps + (q.p_per_channel ? ch : 0);
+            float* cy = q.carry + r0 * q.D + ch;
+            float vv[kScanBatch], pv[kScanBatch];
+#pragma unroll
+            for (int j = 0; j < kScanBatch; ++j) {
+                const int64_t r = step * min(j, n - 1);
+                vv[j] = v[r * q.D];
+                pv[j] = pp[r * ps];
+            }
+#pragma unroll
+            for (int j = 0; j < kScanBatch; ++j) {
+                if (j < n) {
+                    cy[step * j * q.D] = S;
+                    S = __builtin_fmaf(pv[j], S, vv[j]);
+                }
+            }
+        }
+        if (q.fin) q.fin[idx] = S;
+    }
+}
+
 template <int SEGS>
 __global__ __launch_bounds__(SEGS * 16) void swr_scan_kernel(ScanParams q) {
     __shared__ float s_P[SEGS][16], s_V[SEGS][16];
@@ -2125,6 +2161,11 @@ hipError_t launch_gate_reduce(const Params& p, int dtype, int D, void* stream) {
 hipError_t launch_scan(const ScanParams& q, void* stream) {
     const int64_t n = q.seqs * (q.D / 16);
     if (n == 0) return hipSuccess;
+    if (q.nruns <= kScanBatch) {
+        hipLaunchKernelGGL(swr_scan_short_kernel, dim3((unsigned)std::min<int64_t>((n + 15) / 16, 1 << 20)), dim3(256),
+                           0, (hipStream_t)stream, q);
+        return hipGetLastError();
+    }
     const dim3 grid((unsigned)std::min<int64_t>(n, 1 << 20));
     if (q.nruns <= kScanShort)
         hipLaunchKernelGGL((swr_scan_kernel<16>), grid, dim3(256), 0, (hipStream_t)stream, q);

@@ -1,7 +1,8 @@
 """GPU parity of the exact recurrence's carrier scan over the runs at the edges
-of its split into segments: fewer runs than segments, one batch of loads a
-segment, and segments of several batches (run_len forces short runs; packed
-heads of 16 channels run the three stages in both directions)."""
+of its split into segments: one batch of loads for all runs, fewer runs than
+segments, one batch of loads a segment, and segments of several batches
+(run_len forces short runs; packed heads of 16 channels run the three stages in
+both directions)."""
 import numpy as np
 import pytest
 
@@ -14,7 +15,7 @@ pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
 
 
-@pytest.mark.parametrize("runs", [1, 2, 15, 17, 127, 128, 129, 511, 513, 1100])
+@pytest.mark.parametrize("runs", [1, 2, 7, 8, 9, 15, 17, 127, 128, 129, 511, 513, 1100])
 @pytest.mark.parametrize("per_channel", [False, True])
 def test_scan_over_runs(runs, per_channel):
     import paper_2512_13921_amd as swr
