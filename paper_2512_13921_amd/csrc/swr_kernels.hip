@@ -965,14 +965,18 @@ __global__ __launch_bounds__(SEGS * 16) void swr_scan_kernel(ScanParams q) {
         __syncthreads();
         float S = q.init ? q.init[seq * q.D + ch] : 0.0f;
         const int last = q.nruns > 0 ? (int)((q.nruns - 1) / len) : 0;   // the last segment with runs
-        for (int s = 0; s < min(sg, last); ++s) {
-            const float Ps = s_P[s][c], Vs = s_V[s][c];
-            if (__builtin_isfinite(Ps) && __builtin_isfinite(Vs)) {
-                S = __builtin_fmaf(Ps, S, Vs);
-            } else {
-                for (int64_t j = s * len; j < (s + 1) * len; ++j) {   // (s < last: a whole segment)
-                    const int64_t r = q.reverse ? q.nruns - 1 - j : j;
-                    S = __builtin_fmaf(pp[r * pstride], S, v[r * q.D]);
+        for (int s = 0; s < min(sg, last); ++s) S = __builtin_fmaf(s_P[s][c], S, s_V[s][c]);
+        if (!__builtin_isfinite(S)) {   // (what is not finite stays so: one test for all segments)
+            S = q.init ? q.init[seq * q.D + ch] : 0.0f;
+            for (int s = 0; s < min(sg, last); ++s) {
+                const float Ps = s_P[s][c], Vs = s_V[s][c];
+                if (__builtin_isfinite(Ps) && __builtin_isfinite(Vs)) {
+                    S = __builtin_fmaf(Ps, S, Vs);
+                } else {
+                    for (int64_t j = s * len; j < (s + 1) * len; ++j) {   // (s < last: a whole segment)
+                        const int64_t r = q.reverse ? q.nruns - 1 - j : j;
+                        S = __builtin_fmaf(pp[r * pstride], S, v[r * q.D]);
+                    }
                 }
             }
         }
