@@ -606,24 +606,37 @@ bool use_chain_bwd(const swr_problem_t* p, const Resolved& r) {
 // Whether a call takes the three stages although it could chain chunks (one
 // decay per head).  The chain reads every input once, but a sequence's chunks
 // wait for one another, about 0.14 us a chunk, and its flags are reset first;
-// the stages read x, b and a (backward: c, dy and a) twice and have no chain.
-// So the stages win where the bytes are few: small problems, and few
-// sequences (`row`: the bytes of one token of all of them), whose bytes grow
-// no faster with the length than the chain does.  Measured, chain against
-// stages, bf16.  Forward: D 64, 4 sequences of 32768 54 / 29 us, 8 of 131072
-// 198 / 164, 16 of 8192 40 / 28, 16 of 32768 79 / 90, 64 of 2048 31 / 29, 128
-// of 2048 42 / 49; D 128, 2 of 131072 171 / 95, 4 of 131072 194 / 151, 8 of
-// 32768 78 / 78, 16 of 8192 44 / 48; float32 D 128 (whose chain runs halves of
-// 64), 4 of 2048 15 / 16, 4 of 8192 30 / 27.  Backward, D 64: 4 of 131072
-// 215 / 160, 8 of 8192 34 / 28, 8 of 32768 74 / 77, 16 of 131072 523 / 468, 32
-// of 131072 928 / 1047; chains of up to 32 chunks are within 10%.
-bool prefer_stages(const swr_problem_t* p, const Resolved& r, bool backward) {
+// the stages read x, b and a (backward: c, dy and a) twice, in two launches
+// more, and have no chain.  So the stages win where chains are long, or have
+// more chunks than places to run, and the bytes are few: few sequences (`row`:
+// the bytes of one token of all of them), whose bytes grow no faster with the
+// length than the chain does, or small problems.  Chain against stages, us:
+//   forward, bf16, heads of 64 in pairs (16-byte slices): 4 sequences of 32768
+//     51 / 34, 16 of 16384 59 / 51, 24 of 1344 17.4 / 14.4, 64 of 384 14.0 / 13.3; but
+//     64 of 1024 17.0 / 19.6, 128 of 384 14.9 / 18.1
+//   heads of 128: 4 of 16384 35.9 / 33.9; but 2 of 4925 17.6 / 19.6, 32 of 160
+//     12.2 / 13.1, 64 of 384 14.5 / 17.3, 16 of 8192 43 / 49; never in float32 (4
+//     of 8192 28 / 30)
+//   8-byte slices or narrower (heads of 64 of an odd count, heads of 32 or 16
+//     one at a time): heads of 64, 11 of 1344 14.5 / 12.6, 255 of 160 18.6 / 14.8;
+//     but 7 of 1024 11.6 / 13.3, 127 of 384 16.8 / 17.6; heads of 16, 64 of 512
+//     11.7 / 10.5; but 8 of 1024 9.5 / 11.4; in float32 chains of 64 chunks on:
+//     heads of 32, 4 of 32768 48 / 35
+//   backward, D 64: 4 of 131072 215 / 160, 8 of 8192 34 / 28, 8 of 32768 74 /
+//     77, 16 of 131072 523 / 468, 32 of 131072 928 / 1047; chains of up to 32
+//     chunks are within 10%.
+bool prefer_stages(const swr_problem_t* p, const Resolved& r, bool backward, bool pair) {
     const int64_t nch = (p->T + swr::chain_tokens() - 1) / swr::chain_tokens();
     const int64_t row = p->B * p->H * p->D * r.es, total = row * p->T;
     if (backward)
         return nch > 32 && (total <= (int64_t)12 << 20 || row <= 512 || (row <= 2048 && nch >= 512));
-    if (r.es == 4 && nch < 64) return false;
-    return total <= (int64_t)24 << 20 || row <= 1024;
+    if (pair)
+        return row <= 1024 || (row <= 2048 && total <= (int64_t)32 << 20) ||
+               (row <= 4096 && total <= (int64_t)16 << 20) || (row <= 8192 && p->T <= 512);
+    if (p->D == 128) return r.es == 2 && nch >= 48 && row <= 1536;
+    const bool d64 = p->D == 64;
+    const bool chained = r.es == 4 ? nch >= 64 : nch >= (d64 ? 11 : 32) || p->B * p->H * nch >= (d64 ? 480 : 256);
+    return chained && (total <= (int64_t)24 << 20 || row <= 1024);
 }
 
 // Sequences of up to 128 tokens (one step of the backward's eight waves) run
@@ -730,7 +743,7 @@ int swr::exact_forward_impl(const swr_problem_t* p, const void* x, const void* a
     bool chain = !pair && use_chain(p, r) && (!scratch || chain_ws(p, r).floats * 4 <= scratch_bytes);
     const bool single = one_run(p, r);   // (needs no array, but is refused where nothing fits)
     const bool fits = pair || chain || stages_fit;
-    if (single || (!r.pc && stages_fit && prefer_stages(p, r, false))) pair = chain = false;
+    if (single || (!r.pc && stages_fit && prefer_stages(p, r, false, pair))) pair = chain = false;
     const int64_t wfloats = pair ? chain_pair_floats(p) : chain ? chain_ws(p, r).floats : w.floats;
     const int64_t seqs = p->B * p->H, sbytes = seqs * p->D * 4;
     if (seqs == 0) return SWR_OK;
@@ -885,7 +898,7 @@ int swr_exact_backward(const swr_problem_t* p, const void* x, const void* a, con
     }
 
     const bool single = one_run(p, r);
-    if (!single && use_chain_bwd(p, r) && !prefer_stages(p, r, true)) {   // one pass: chunks from the sequences' ends, chained by a look-back
+    if (!single && use_chain_bwd(p, r) && !prefer_stages(p, r, true, false)) {   // one pass: chunks from the sequences' ends, chained by a look-back
         const ChainWs cw = chain_ws(p, r);
         float* f = (float*)workspace;
         swr::Params k = make_params(p, r, true);

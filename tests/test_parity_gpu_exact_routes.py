@@ -1,7 +1,7 @@
 """GPU parity of the exact recurrence on both sides of the sizes where its
-schedule changes: a single run (up to 128 tokens), the three stages (few bytes
-or few sequences), the one-pass chains; and the count of look-back waits that
-gave up, which reads zero whichever schedule ran."""
+schedule changes: a single run (up to 128 tokens), the three stages (long
+chains or many chunks of few bytes), the one-pass chains; and the count of
+look-back waits that gave up, which reads zero whichever schedule ran."""
 import numpy as np
 import pytest
 
@@ -25,11 +25,26 @@ CASES = [
     (1, 4096, 2, 64, 64, "bf16", False),     # the backward's last chain of 32 chunks
     (1, 4097, 2, 64, 64, "bf16", False),     # and its first 33 chunks in three stages
     (2, 8192, 3, 64, 128, "f32", False),     # float32: 64 chunks, 12.6 MB (backward one-pass)
-    (1, 8100, 3, 128, 16, "f32", False),     # float32: 64 chunks, three stages
-    (1, 8000, 3, 128, 16, "f32", False),     # float32: 63 chunks, one pass
+    (1, 8100, 3, 64, 16, "f32", False),      # float32: 64 chunks, three stages
+    (1, 8000, 3, 64, 16, "f32", False),      # float32: 63 chunks, one pass
+    (1, 8100, 3, 128, 16, "f32", False),     # float32 heads of 128: one pass at any length
+    (1, 8000, 3, 128, 16, "f32", False),
     (1, 50000, 4, 128, 128, "bf16", False),  # a row of 1024 bytes: three stages, over 24 MB
     (1, 50000, 6, 64, 128, "bf16", False),   # a row of 768 bytes: pairs would chain
     (1, 33000, 3, 128, 64, "f32", False),    # over 24 MB and 1024 bytes: one pass
+    (1, 6017, 6, 128, 64, "bf16", False),    # a row of 1536 bytes, 48 chunks: three stages
+    (1, 6016, 6, 128, 64, "bf16", False),    # 47 chunks: one pass
+    (1, 6017, 7, 128, 64, "bf16", False),    # a longer row: one pass
+    (1, 600, 32, 64, 64, "bf16", False),     # pairs, a row of 4096 bytes, few bytes: three stages
+    (1, 600, 34, 64, 64, "bf16", False),     # of more: one pass past 512 tokens
+    (2, 512, 32, 64, 64, "bf16", False),     # (three stages up to there, to 8192 bytes)
+    (1, 513, 48, 64, 64, "bf16", False),
+    (1, 1281, 5, 64, 32, "bf16", False),     # heads of 64 of an odd count: 11 chunks, three stages
+    (1, 1280, 5, 64, 32, "bf16", False),     # 10 chunks, one pass
+    (1, 400, 121, 64, 16, "bf16", False),    # 484 chunks in all, three stages
+    (1, 400, 119, 64, 16, "bf16", False),    # 476 chunks, one pass
+    (1, 950, 33, 32, 64, "bf16", False),     # heads of 32 one at a time: 264 chunks, three stages
+    (1, 950, 31, 32, 64, "bf16", False),     # 248 chunks, one pass
 ]
 
 
