@@ -40,9 +40,12 @@ int64_t pick_run_len(int64_t T, int64_t seqs, int64_t step, int64_t target) {
 //     ceil(workgroups / cap) * (run + halo / 2)
 // after another, of which the run length with the least is taken: a grid just
 // over a round would cost a whole one more (the uniform backward of 4 x 7 heads
-// of 64, T 61554: 268 workgroups where 256 fit, 802 us; 252, 477 us).  Where
-// runs of `len` tokens (0: never) make two rounds or more, they are taken:
-// short runs then even out the workgroups' ends.
+// of 64, T 61554: 268 workgroups where 256 fit, 802 us; 252, 477 us).  Equal
+// costs go to more rounds, except of single steps, whose halo costs more than
+// the model's (the uniform backward of 96 x 8 steps of 128 tokens: runs of 4
+// steps 39 us, of one 44).  Where runs of `len` tokens (0: never) make two
+// rounds or more, about that length is taken: short runs then even out the
+// workgroups' ends.
 struct Sweep {
     int64_t cap, len;
 };
@@ -60,7 +63,7 @@ int64_t plan_run_len(int64_t T, int64_t units, int64_t step, int64_t halo, const
         const int64_t r = std::min(nsteps, k * s.cap / units);
         const int64_t steps = (nsteps + r - 1) / r, runs = (nsteps + steps - 1) / steps;
         const int64_t c = (units * runs + s.cap - 1) / s.cap * (2 * steps * step + (runs > 1 ? halo : 0));
-        if (cost < 0 || c <= cost) { best = steps; cost = c; }
+        if (cost < 0 || c < cost || (c == cost && steps > 1)) { best = steps; cost = c; }
     }
     return best * step;
 }
@@ -68,14 +71,13 @@ int64_t plan_run_len(int64_t T, int64_t units, int64_t step, int64_t halo, const
 // The backward's sweeps.  8 waves (l = 128): one workgroup a compute unit (165
 // to 254 VGPRs), two of lanes of 1 or 2 channels (82 to 127; recomputing its
 // carriers 2 channels a lane take up to 142); one round, since the runs' ends
-// cost less than further halos.  4 waves: two (three of packed heads, 165 VGPRs,
-// and of float32 heads of 64, 150), or four of the narrow ones, and
-// runs of 256 tokens once those make several rounds (512 for heads of 128 and
-// bf16 heads of 64, 128 for float32 lanes of 1 or 2 channels and with a decay per
-// channel), or twice that for bf16 heads of 64 or more without saved
-// carriers, whose halo is a step longer.  Against fixed grids of 256, 1024 (128
-// channels) and 8192 workgroups, bf16, saved carriers: D 64, l 64, 16 heads of
-// 16384 tokens 68.2 -> 48 us, of 65536 235 -> 211; a decay per channel, D 128,
+// cost less than further halos.  4 waves: two (three of packed heads, 165
+// VGPRs), or four of the narrow ones, and runs of 256 tokens once those make
+// several rounds (512 for heads of 128 and bf16 heads of 64, 128 for float32
+// with a decay per channel), or twice that for bf16 heads of 64 or more without
+// saved carriers, whose halo is a step longer.  Against fixed grids of 256, 1024
+// (128 channels) and 8192 workgroups, bf16, saved carriers: D 64, l 64, 16 heads
+// of 16384 tokens 68.2 -> 48 us, of 65536 235 -> 211; a decay per channel, D 128,
 // l 64, 16 of 8192 95 -> 74; D 48, l 128, 48 of 24448 438 -> 299.
 struct Resolved;
 Sweep bwd_sweep(const Resolved& r, bool recompute);
@@ -136,28 +138,54 @@ struct Resolved {
     int64_t carriers;   // float32 carriers of the whole problem
 };
 
+// The call that a plan is for.
+enum class Use {
+    kForward,     // the jagged window's forward: heads may run in pairs
+    kBackward,    // its backward, from saved carriers
+    kRecompute,   // its backward without them
+    kExact,       // the exact recurrence, either direction
+};
+
+bool sigmoids(const swr_problem_t* p) { return (p->flags & (SWR_FLAG_SIGMOID_DECAY | SWR_FLAG_SIGMOID_PREGATE)) != 0; }
+
 Sweep bwd_sweep(const Resolved& r, bool recompute) {
     if (r.bwd.tw * r.bwd.hw == 8) return {r.cpl >= 4 || (r.cpl == 2 && recompute) ? 256 : 512, 0};
-    if (r.cpl <= 2) return {1024, r.es == 4 ? 128 : 256};
+    if (r.cpl <= 2) return {1024, 256};
     if (r.pack > 1) return {recompute ? 512 : 768, 256};
     const int64_t len = r.cpl == 8 || (r.es == 2 && !r.pc) ? 512 : r.pc && r.es == 4 ? 128 : 256;
     // (a decay per channel: heads in four parts, or that leave lanes idle, ran
     // as fast or faster with twice the workgroups)
-    const int64_t cap = r.pc && (r.hshift == 2 || r.nlane < 16) ? 1024 : r.cpl == 4 && r.es == 4 && !r.pc ? 768 : 512;
+    const int64_t cap = r.pc && (r.hshift == 2 || r.nlane < 16) ? 1024 : 512;
     return {cap, recompute && r.es == 2 && !r.pc ? 2 * len : len};
 }
 
-// The backward's launch plan (recompute: without saved carriers).
-void plan_backward(const swr_problem_t* p, Resolved* r, bool recompute) {
+// Whether the backward keeps a fixed grid of short runs (about 8192, of heads of
+// 128 about 1024): where the plan above gains nothing over it.  4 waves, random
+// problems, time of the plan over that of the grid: float32 lanes of up to 4
+// channels 0.85 to 1.11, 1.004 on average over 54 (packed 1.005 over 33); a decay
+// per channel with up to 2 channels a lane 0.80 to 1.30, 1.003 over 66; bf16
+// lanes of 4 channels with the fused sigmoids 0.94 to 1.17, 1.005 over 26.  The
+// exact recurrence's runs have no halo: packed bf16 heads 0.97 to 1.11, 1.022
+// over 90; float32 0.91 to 1.14, 1.017 over 43.
+bool keeps_short_runs(const swr_problem_t* p, const Resolved& r, Use use) {
+    if (r.bwd.tw != 4) return false;
+    if (use == Use::kExact && (r.es == 4 || r.pack > 1)) return true;
+    if (r.cpl > 4) return false;
+    if (r.pc) return r.cpl <= 2;
+    return r.es == 4 || (sigmoids(p) && r.cpl == 4 && r.pack == 1);
+}
+
+// The backward's launch plan.
+void plan_backward(const swr_problem_t* p, Resolved* r, Use use) {
     const int64_t groups = p->B * r->hv / r->bwd.hw;   // work items per run position
     if (p->run_len > 0)
         r->run_len = p->run_len;
     else if (r->empty)
         r->run_len = r->step;
-    else if (r->pack > 1 && r->es == 4 && r->bwd.tw == 4)   // (within 7% of the plan either way)
-        r->run_len = pick_run_len(p->T, groups, r->step, 8192);
+    else if (keeps_short_runs(p, *r, use))
+        r->run_len = pick_run_len(p->T, groups, r->step, r->cpl == 8 ? 1024 : 8192);
     else
-        r->run_len = plan_run_len(p->T, groups, r->step, p->block, bwd_sweep(*r, recompute));
+        r->run_len = plan_run_len(p->T, groups, r->step, p->block, bwd_sweep(*r, use == Use::kRecompute));
     r->nruns = r->empty ? 0 : (p->T + r->run_len - 1) / r->run_len;
     r->nwork = groups * r->nruns;
 }
@@ -172,7 +200,8 @@ bool packed_offsets_fit(const swr_problem_t* p, int64_t pack) {
            p->sa_t <= (lim - (pack - 1) * p->sa_h * 4) / 64 && p->T / p->block < lim / (pack * p->D * 4);
 }
 
-int resolve(const swr_problem_t* p, Resolved* r, bool allow_pack = true, bool allow_pair = false) {
+// together: heads may be packed or run in pairs (false: each on its own).
+int resolve(const swr_problem_t* p, Resolved* r, Use use, bool together = true) {
     if (!p) return SWR_ERR_NULL;
     if (p->abi_version != SWR_ABI_VERSION) return SWR_ERR_VERSION;
     if (p->dtype != SWR_DTYPE_F32 && p->dtype != SWR_DTYPE_BF16) return SWR_ERR_DTYPE;
@@ -221,9 +250,9 @@ int resolve(const swr_problem_t* p, Resolved* r, bool allow_pack = true, bool al
     // T 4096 would take 7.3 against 6.6); in float32 the forward only (2 x 7, T
     // 65536 78 -> 53; the backward of 2 x 5 would take 91 against 80).  A forced
     // run length, tuned with the heads one by one, keeps them so.
-    if (allow_pack && !r->pc && (p->D == 16 || p->D == 32) && p->sx_h == p->D && packed_offsets_fit(p, 64 / p->D) &&
+    if (together && !r->pc && (p->D == 16 || p->D == 32) && p->sx_h == p->D && packed_offsets_fit(p, 64 / p->D) &&
         (p->H % (64 / p->D) == 0 ||
-         (p->H >= 2 && !r->empty && p->run_len == 0 && (r->es == 2 || allow_pair) && p->B * p->H * p->T >= 32768))) {
+         (p->H >= 2 && !r->empty && p->run_len == 0 && (r->es == 2 || use == Use::kForward) && p->B * p->H * p->T >= 32768))) {
         r->pack = (int)(64 / p->D);
         r->dk = 64;
     }
@@ -236,7 +265,7 @@ int resolve(const swr_problem_t* p, Resolved* r, bool allow_pack = true, bool al
     // head's carriers, which must keep every 32-bit lane offset below 2^31
     // bytes.)
     const int64_t lim32 = 0x7fffffffLL;
-    r->pair = allow_pair && !r->pc && p->D == 64 && p->dtype == SWR_DTYPE_BF16 && p->H % 2 == 0 &&
+    r->pair = together && use == Use::kForward && !r->pc && p->D == 64 && p->dtype == SWR_DTYPE_BF16 && p->H % 2 == 0 &&
               (p->sx_h * 2) % 16 == 0 && p->sx_h >= 0 && p->sx_h <= (int64_t)1 << 26 && p->sa_h >= 0 &&
               p->sa_h <= (int64_t)1 << 26 && p->sx_t >= 0 && p->sx_t <= (lim32 - p->sx_h * 2 - 128) / 32 &&
               p->sa_t >= 0 && p->sa_t <= (lim32 - p->sa_h * 4) / 64 &&
@@ -260,7 +289,7 @@ int resolve(const swr_problem_t* p, Resolved* r, bool allow_pack = true, bool al
         if (g * ((p->T + rl - 1) / rl) < fwd_workgroups(r->fwd)) r->fwd = swr::fwd_shape_single();
     }
     const int64_t groups = seqs / r->fwd.hw;       // forward work items per run position
-    plan_backward(p, r, false);
+    plan_backward(p, r, use);
     if (p->run_len > 0) {
         r->run_len_f = p->run_len;
     } else if (r->empty) {
@@ -299,19 +328,16 @@ int check_strides_aligned(const swr_problem_t* p, const Resolved& r) {
 
 bool aligned(const void* ptr, int64_t bytes) { return ((uintptr_t)ptr % (uintptr_t)bytes) == 0; }
 
-// resolve() for a call with these [B,T,H,D] tensors: packed small heads need
-// each lane's 64-channel row slice aligned (8 or 16 bytes); otherwise the
-// heads run one by one.
-// The same for paired 64-channel heads (allow_pair: the jagged window's
-// forward and backward), which need 16-byte aligned slices.
-int resolve_for(const swr_problem_t* p, Resolved* r, std::initializer_list<const void*> xs,
-                bool allow_pair = false) {
-    int rc = resolve(p, r, true, allow_pair);
+// resolve() for a call with these [B,T,H,D] tensors: packed small heads and
+// pairs need each lane's row slice aligned (8 or 16 bytes); otherwise the heads
+// run one by one.
+int resolve_for(const swr_problem_t* p, Resolved* r, Use use, std::initializer_list<const void*> xs) {
+    int rc = resolve(p, r, use);
     if (rc != SWR_OK || (r->pack == 1 && !r->pair) || r->empty) return rc;
     bool ok = check_strides_aligned(p, *r) == SWR_OK;
     for (const void* q : xs)
         if (q && !aligned(q, r->vbytes)) ok = false;
-    return ok ? SWR_OK : resolve(p, r, false, false);
+    return ok ? SWR_OK : resolve(p, r, use, false);
 }
 
 struct Span {
@@ -388,9 +414,9 @@ int swr_launch_info(const swr_problem_t* problem, int64_t* fwd_run_len, int64_t*
     // the plans of swr_forward (which may pair heads) and swr_backward, with
     // suitably aligned pointers
     Resolved r, f;
-    int rc = resolve(problem, &r);
+    int rc = resolve(problem, &r, Use::kBackward);
     if (rc != SWR_OK) return rc;
-    if ((rc = resolve(problem, &f, true, true)) != SWR_OK) return rc;
+    if ((rc = resolve(problem, &f, Use::kForward)) != SWR_OK) return rc;
     if (fwd_run_len) *fwd_run_len = f.run_len_f;
     if (fwd_workgroups) *fwd_workgroups = f.nwork_f;
     if (bwd_run_len) *bwd_run_len = r.run_len;
@@ -400,7 +426,7 @@ int swr_launch_info(const swr_problem_t* problem, int64_t* fwd_run_len, int64_t*
 
 int64_t swr_carrier_elems(const swr_problem_t* problem) {
     Resolved r;
-    const int rc = resolve(problem, &r);
+    const int rc = resolve(problem, &r, Use::kBackward);
     return rc != SWR_OK ? rc : r.carriers;
 }
 
@@ -410,7 +436,7 @@ namespace {
 int forward_impl(const swr_problem_t* p, const void* x, const void* a, const void* b,
                  const void* c, void* y, float* carriers, void* stream) {
     Resolved r;
-    int rc = resolve_for(p, &r, {x, b, c, (const void*)y}, true);
+    int rc = resolve_for(p, &r, Use::kForward, {x, b, c, (const void*)y});
     if (rc != SWR_OK) return rc;
     if (r.empty) return SWR_OK;
     if (!x || !a || !b || (y && !c)) return SWR_ERR_NULL;
@@ -436,7 +462,7 @@ int forward_impl(const swr_problem_t* p, const void* x, const void* a, const voi
 int swr_forward(const swr_problem_t* p, const void* x, const void* a, const void* b,
                 const void* c, void* y, float* carriers, void* stream) {
     Resolved r;
-    const int rc = resolve(p, &r);
+    const int rc = resolve(p, &r, Use::kBackward);
     if (rc != SWR_OK) return rc;
     if (!r.empty && !y) return SWR_ERR_NULL;
     return forward_impl(p, x, a, b, c, y, carriers, stream);
@@ -445,7 +471,7 @@ int swr_forward(const swr_problem_t* p, const void* x, const void* a, const void
 int swr_carriers(const swr_problem_t* p, const void* x, const void* a, const void* b,
                  float* carriers, void* stream) {
     Resolved r;
-    const int rc = resolve(p, &r);
+    const int rc = resolve(p, &r, Use::kBackward);
     if (rc != SWR_OK) return rc;
     if (!r.empty && !carriers) return SWR_ERR_NULL;
     return forward_impl(p, x, a, b, nullptr, nullptr, carriers, stream);
@@ -455,7 +481,8 @@ int swr_backward(const swr_problem_t* p, const void* x, const void* a, const voi
                  const void* c, const void* dy, const float* carriers, void* dx, float* da,
                  void* db, void* dc, void* stream) {
     Resolved r;
-    int rc = resolve_for(p, &r, {x, b, c, dy, (const void*)dx, (const void*)db, (const void*)dc});
+    int rc = resolve_for(p, &r, carriers ? Use::kBackward : Use::kRecompute,
+                         {x, b, c, dy, (const void*)dx, (const void*)db, (const void*)dc});
     if (rc != SWR_OK) return rc;
     if (r.empty) return SWR_OK;
     // (carriers may be NULL: the kernels then recompute them)
@@ -477,7 +504,6 @@ int swr_backward(const swr_problem_t* p, const void* x, const void* a, const voi
             if (overlap(outs[i], outs[j])) return SWR_ERR_ALIAS;
     }
 
-    if (!carriers) plan_backward(p, &r, true);
     swr::Params k = make_params(p, r, true);
     k.x = x; k.a = a; k.b = b; k.c = c; k.dy = dy;
     k.dx = dx; k.da = da; k.db = db; k.dc = dc;
@@ -660,7 +686,7 @@ int64_t chain_pair_floats(const swr_problem_t* p) {
 // pointers are checked where there are any: resolve_for).
 bool shape_pairs(const swr_problem_t* p) {
     Resolved t;
-    return resolve(p, &t, true, true) == SWR_OK && t.pair && !t.empty && t.hv < ((int64_t)1 << 30);
+    return resolve(p, &t, Use::kForward) == SWR_OK && t.pair && !t.empty && t.hv < ((int64_t)1 << 30);
 }
 
 // Workspace of the exact calls for one plan: the three-stage arrays (the
@@ -698,10 +724,10 @@ int64_t swr_exact_workspace_bytes(const swr_problem_t* problem) {
     // enough for either launch plan (packed small heads or not), since the
     // pointers of the later call decide between them
     Resolved r, u;
-    int rc = resolve(problem, &r, true);
+    int rc = resolve(problem, &r, Use::kExact);
     if (rc != SWR_OK) return rc;
     if (!r.natural) return SWR_ERR_UNSUPPORTED;
-    if ((rc = resolve(problem, &u, false)) != SWR_OK) return rc;
+    if ((rc = resolve(problem, &u, Use::kExact, false)) != SWR_OK) return rc;
     return std::max(exact_ws_floats(problem, r), exact_ws_floats(problem, u)) * 4;
 }
 
@@ -717,13 +743,13 @@ int swr::exact_forward_impl(const swr_problem_t* p, const void* x, const void* a
                             const void* c, const float* h0, void* y, float* carriers, float* h_last,
                             void* workspace, ScratchFn scratch, int64_t scratch_bytes, void* stream) {
     Resolved r;
-    int rc = resolve_for(p, &r, {x, b, c, (const void*)y});
+    int rc = resolve_for(p, &r, Use::kExact, {x, b, c, (const void*)y});
     if (rc != SWR_OK) return rc;
     if (!r.natural) return SWR_ERR_UNSUPPORTED;
     // (packed heads of a count that fills no whole virtual head: the chain of
     // the heads one by one may fit the static array where the stages do not)
     if (scratch && r.pack > 1 && p->H % r.pack && exact_ws(p, r, true).floats * 4 > scratch_bytes &&
-        (rc = resolve(p, &r, false)) != SWR_OK)
+        (rc = resolve(p, &r, Use::kExact, false)) != SWR_OK)
         return rc;
     ExactWs w = exact_ws(p, r, scratch != nullptr);
     // the library's static array may hold the three stages' arrays but not the
@@ -738,8 +764,9 @@ int swr::exact_forward_impl(const swr_problem_t* p, const void* x, const void* a
     }
     const bool stages_fit = !scratch || w.floats * 4 <= scratch_bytes;
     Resolved rp;
-    bool pair = SWR_EXACT_CHAIN_PAIR && use_chain(p, r) && !r.pc && resolve_for(p, &rp, {x, b, c, (const void*)y}, true) == SWR_OK &&
-                rp.pair && (!scratch || chain_pair_floats(p) * 4 <= scratch_bytes);
+    bool pair = SWR_EXACT_CHAIN_PAIR && use_chain(p, r) && !r.pc &&
+                resolve_for(p, &rp, Use::kForward, {x, b, c, (const void*)y}) == SWR_OK && rp.pair &&
+                (!scratch || chain_pair_floats(p) * 4 <= scratch_bytes);
     bool chain = !pair && use_chain(p, r) && (!scratch || chain_ws(p, r).floats * 4 <= scratch_bytes);
     const bool single = one_run(p, r);   // (needs no array, but is refused where nothing fits)
     const bool fits = pair || chain || stages_fit;
@@ -866,7 +893,7 @@ int swr_exact_backward(const swr_problem_t* p, const void* x, const void* a, con
                        const float* dh_last, void* dx, float* da, void* db, void* dc, float* dh0,
                        void* workspace, void* stream) {
     Resolved r;
-    int rc = resolve_for(p, &r, {x, b, c, dy, (const void*)dx, (const void*)db, (const void*)dc});
+    int rc = resolve_for(p, &r, Use::kExact, {x, b, c, dy, (const void*)dx, (const void*)db, (const void*)dc});
     if (rc != SWR_OK) return rc;
     if (!r.natural) return SWR_ERR_UNSUPPORTED;
     const ExactWs w = exact_ws(p, r);
@@ -981,7 +1008,7 @@ int check_step_strides(const swr_problem_t* p, const Resolved& r, int64_t vb) {
 int step_impl(const swr_problem_t* p, int64_t t0, const void* x, const void* a, const void* b,
               const void* c, void* y, float* state, bool exact, void* stream) {
     Resolved r;
-    int rc = resolve(p, &r);
+    int rc = resolve(p, &r, Use::kBackward);
     if (rc != SWR_OK) return rc;
     if (!r.natural) return SWR_ERR_UNSUPPORTED;
     if (t0 < 0) return SWR_ERR_SHAPE;
@@ -1030,7 +1057,7 @@ int swr_exact_step(const swr_problem_t* problem, const void* x, const void* a, c
 int swr_decode_state(const swr_problem_t* p, const void* a, const float* carriers, float* state,
                      void* stream) {
     Resolved r;
-    const int rc = resolve(p, &r);
+    const int rc = resolve(p, &r, Use::kBackward);
     if (rc != SWR_OK) return rc;
     if (!r.natural) return SWR_ERR_UNSUPPORTED;
     const int64_t seqs = p->B * p->H;
@@ -1076,7 +1103,7 @@ struct UniPlan {
 };
 
 int uni_resolve(const swr_problem_t* p, UniPlan* u, bool backward) {
-    int rc = resolve(p, &u->r, false);
+    int rc = resolve(p, &u->r, Use::kBackward, false);
     if (rc != SWR_OK) return rc;
     if (!u->r.natural) return SWR_ERR_UNSUPPORTED;
     if (p->flags & SWR_FLAG_PER_CHANNEL_DECAY) return SWR_ERR_UNSUPPORTED;
@@ -1201,7 +1228,7 @@ namespace {
 // window (no per-channel decay, no packing), then the group and the gate
 // tensors' strides.  gspan receives the bytes spanned by one gate tensor.
 int gates_resolve(const swr_problem_t* p, int64_t group, const int64_t* gst, Resolved* r, int64_t* gspan) {
-    int rc = resolve(p, r, false);
+    int rc = resolve(p, r, Use::kBackward, false);
     if (rc != SWR_OK) return rc;
     if (!r->natural) return SWR_ERR_UNSUPPORTED;
     if (p->flags & SWR_FLAG_PER_CHANNEL_DECAY) return SWR_ERR_UNSUPPORTED;
@@ -1232,7 +1259,7 @@ extern "C" {
 
 int64_t swr_shared_gates_workspace_bytes(const swr_problem_t* p, int64_t group) {
     Resolved r;
-    const int rc = resolve(p, &r, false);
+    const int rc = resolve(p, &r, Use::kBackward, false);
     if (rc != SWR_OK) return rc;
     if (!r.natural) return SWR_ERR_UNSUPPORTED;
     if (group < 1 || (p->H > 0 && p->H % group != 0)) return SWR_ERR_SHAPE;
