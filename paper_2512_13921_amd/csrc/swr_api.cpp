@@ -200,6 +200,31 @@ bool packed_offsets_fit(const swr_problem_t* p, int64_t pack) {
            p->sa_t <= (lim - (pack - 1) * p->sa_h * 4) / 64 && p->T / p->block < lim / (pack * p->D * 4);
 }
 
+// Whether heads of 16 or 32 channels stored next to each other run as packed
+// 64-channel virtual heads on the per-channel kernels (a lane slice of one such
+// head would be 2-4 bytes); the caller's pointers may still veto it (alignment),
+// see resolve_for.  A head count that does not divide leaves lanes of the last
+// virtual head idle, which still beats the narrow slices once there is work for
+// the machine (bf16, 2 x 7 heads of 16, T 65536, l 64: forward 78 -> 34 us,
+// backward 60 -> 43; 2 x 5, T 4096 7.8 -> 7.5; 2 x 3, T 4096 would take 7.3
+// against 6.6; the forward at l 128, whose runs are longer, from twice as much
+// on: 7 of 16, T 12194 11.0 -> 10.1, T 5888 would take 9.6 against 7.7); in
+// float32 the forward only (2 x 7, T 65536 78 -> 53; the backward of 2 x 5 would
+// take 91 against 80); and of heads of 32 at l < 128 not the backward with the
+// fused sigmoids (16 x 3, T 29532, l 16 would take 263 us against 193; 7, T
+// 27392 33 against 27) or without saved carriers (8 x 5, T 69361, l 32 405
+// against 352; even on average over 16 problems).  A forced run length, tuned
+// with the heads one by one, keeps them so.
+bool packs(const swr_problem_t* p, const Resolved& r, Use use) {
+    if (r.pc || (p->D != 16 && p->D != 32) || p->sx_h != p->D || !packed_offsets_fit(p, 64 / p->D)) return false;
+    if (p->H % (64 / p->D) == 0) return true;
+    if (r.empty || p->H < 2 || p->run_len != 0 || (r.es == 4 && use != Use::kForward)) return false;
+    if (p->D == 32 && p->block < 128 &&
+        (use == Use::kRecompute || (use == Use::kBackward && sigmoids(p))))
+        return false;
+    return p->B * p->H * p->T >= (use == Use::kForward && p->block == 128 ? 65536 : 32768);
+}
+
 // together: heads may be packed or run in pairs (false: each on its own).
 int resolve(const swr_problem_t* p, Resolved* r, Use use, bool together = true) {
     if (!p) return SWR_ERR_NULL;
@@ -240,19 +265,7 @@ int resolve(const swr_problem_t* p, Resolved* r, Use use, bool together = true) 
     r->dk = r->dv <= 16 ? 16 : r->dv <= 32 ? 32 : r->dv <= 64 ? 64 : 128;
     r->natural = p->D == 16 || p->D == 32 || p->D == 64 || p->D == 128;
     r->pack = 1;
-    // Heads of 16 or 32 channels stored next to each other run as packed
-    // 64-channel virtual heads on the per-channel kernels (a lane slice of one
-    // such head would be 2-4 bytes); the caller's pointers may still veto it
-    // (alignment), see resolve_for.  A head count that does not divide leaves
-    // lanes of the last virtual head idle, which still beats the narrow slices
-    // once there is work for the machine (bf16, 2 x 7 heads of 16, T 65536, l
-    // 64: forward 78 -> 34 us, backward 60 -> 43; 2 x 5, T 4096 7.8 -> 7.5; 2 x 3,
-    // T 4096 would take 7.3 against 6.6); in float32 the forward only (2 x 7, T
-    // 65536 78 -> 53; the backward of 2 x 5 would take 91 against 80).  A forced
-    // run length, tuned with the heads one by one, keeps them so.
-    if (together && !r->pc && (p->D == 16 || p->D == 32) && p->sx_h == p->D && packed_offsets_fit(p, 64 / p->D) &&
-        (p->H % (64 / p->D) == 0 ||
-         (p->H >= 2 && !r->empty && p->run_len == 0 && (r->es == 2 || use == Use::kForward) && p->B * p->H * p->T >= 32768))) {
+    if (together && packs(p, *r, use)) {
         r->pack = (int)(64 / p->D);
         r->dk = 64;
     }

@@ -84,3 +84,19 @@ def test_short_runs_of_very_long_sequences_fit_a_launch(B, T, H, D, block, dtype
         assert 0 < i["fwd_workgroups"] < 2 ** 31 and 0 < i["bwd_workgroups"] < 2 ** 31
     if D != 112:
         assert swr.swr_exact_workspace_bytes(p) > 0
+
+
+@pytest.mark.parametrize("D,block,sigmoid,packed", [(32, 64, True, False), (32, 128, True, True), (32, 64, False, True),
+                                                    (16, 64, True, True)])
+def test_odd_counts_with_sigmoids(D, block, sigmoid, packed):
+    B, T, H = 2, 8192, 3
+    p = swr.make_problem(B, T, H, D, block, swr.SWR_DTYPE_BF16, (T * H * D, H * D, D), (T * H, H, 1),
+                         sigmoid_decay=sigmoid)
+    i = swr.swr_launch_info(p)
+    assert i["bwd_workgroups"] // -(-T // i["bwd_run_len"]) == (B * -(-H * D // 64) if packed else B * H)
+
+
+@pytest.mark.parametrize("T,packed", [(10922, False), (10923, True)])
+def test_odd_counts_in_the_forward_of_long_blocks(T, packed):
+    i = swr.swr_launch_info(swr.make_problem(2, T, 3, 16, 128, swr.SWR_DTYPE_BF16, (T * 48, 48, 16), (T * 3, 3, 1)))
+    assert i["fwd_workgroups"] // -(-T // i["fwd_run_len"]) == (2 if packed else 6)
