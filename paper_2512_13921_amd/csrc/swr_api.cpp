@@ -1301,8 +1301,8 @@ int swr_forward_shared_gates(const swr_problem_t* p, int64_t group, const int64_
     swr::Params k = make_params(p, r, false);
     set_gates(&k, group, gate_strides);
     k.x = x; k.a = a; k.b = b; k.c = c; k.y = y; k.carriers = carriers;
-    return swr::launch(k, p->dtype, r.dk, r.fwd, false, false, 1, swr::kGrouped, stream) == hipSuccess
-               ? SWR_OK : SWR_ERR_HIP;
+    const int mode = group == 1 ? swr::kOwnGates : swr::kGrouped;
+    return swr::launch(k, p->dtype, r.dk, r.fwd, false, false, 1, mode, stream) == hipSuccess ? SWR_OK : SWR_ERR_HIP;
 }
 
 int swr_backward_shared_gates(const swr_problem_t* p, int64_t group, const int64_t* gate_strides,

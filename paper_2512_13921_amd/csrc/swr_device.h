@@ -89,7 +89,8 @@ constexpr int kFwdLoad = SWR_FWD_LOAD_POLICY;
 // The forward's loads of b and c shared by groups of heads keep the default:
 // the group's other workgroups read the same rows from the L2 that the hint
 // would drop them from (B8 T16384 H16 D128, groups of 2: 331 -> 313 us, of 4:
-// 334 -> 293).
+// 334 -> 293).  Groups of one keep the hint (372 against 364; float32 B4 T8192
+// H32 D64 198 against 191).
 constexpr int kSharedGateLoad = 0;
 constexpr int kFwdStore = SWR_FWD_STORE_POLICY;
 constexpr int kBwdLoad = SWR_BWD_LOAD_POLICY;

@@ -75,7 +75,8 @@ __device__ inline void clear_time_outs(const Params& p) {
 // of each run started from zero and the run's decay product -- (kAggregate),
 // or the outputs from the exact state entering each run (kExact).  The exact
 // modes need no halo and never restart the carrier.  kGrouped is the jagged
-// window with b and c shared by groups of p.group heads (their own strides).
+// window with b and c shared by groups of p.group heads (their own strides),
+// kOwnGates the same with a group a head.
 // kPaired is the jagged window on heads of D/2 channels taken two at a time
 // (work item h = heads 2h, 2h+1): each 16-lane row holds both heads' rows,
 // lanes 0-7 the first head's channels and 8-15 the second's, so every lane
@@ -84,10 +85,10 @@ __device__ inline void clear_time_outs(const Params& p) {
 // and every lane keeps its own head's result.
 template <class IO, int CPL, int TW, int HW, bool FEAT, int MODE>
 __global__ __launch_bounds__(TW * HW * 64, 3) void swr_fwd_kernel(Params p) {
-    constexpr bool GG = MODE == kGrouped;
+    constexpr bool GG = MODE == kGrouped || MODE == kOwnGates;
     constexpr bool PAIR = MODE == kPaired;
     constexpr bool SWR = MODE == kSwr || GG || PAIR;
-    constexpr int kGateLoad = GG ? kSharedGateLoad : Stream<IO, CPL>::load;   // of b and c
+    constexpr int kGateLoad = MODE == kGrouped ? kSharedGateLoad : Stream<IO, CPL>::load;   // of b and c
     constexpr int NH = PAIR ? 2 : 1;   // heads per kernel head
     const int sig_a = FEAT ? p.sig_a : 0, sig_b = FEAT ? p.sig_b : 0;   // fused featurisation
     constexpr int NW = TW * HW;
@@ -1964,7 +1965,7 @@ static hipError_t launch_pc_mode(const Params& p, const Shape& sh, bool backward
 
 template <class IO, int CPL, bool FEAT, int MODE>
 static hipError_t launch_shape(const Params& p, const Shape& sh, bool backward, hipStream_t stream) {
-    if constexpr (MODE == kPaired) {   // a forward-only mode
+    if constexpr (MODE == kPaired || MODE == kOwnGates) {   // forward-only modes
         if (backward) return hipErrorInvalidValue;
     }
     if constexpr (MODE == kRecompute) {
@@ -1980,7 +1981,7 @@ static hipError_t launch_shape(const Params& p, const Shape& sh, bool backward, 
             SWR_LAUNCH((swr_bwd_agg_kernel<IO, CPL, 8, FEAT>), 8, 1)
             SWR_LAUNCH((swr_bwd_agg_kernel<IO, CPL, 4, FEAT>), 4, 1)
             else return hipErrorInvalidValue;
-        } else if constexpr (MODE != kPaired) {
+        } else if constexpr (MODE != kPaired && MODE != kOwnGates) {
             if (false) {}
             SWR_LAUNCH((swr_bwd_kernel<IO, CPL, 8, 1, FEAT, MODE>), 8, 1)
             SWR_LAUNCH((swr_bwd_kernel<IO, CPL, 4, 1, FEAT, MODE>), 4, 1)
@@ -2003,6 +2004,7 @@ static hipError_t launch_mode(const Params& p, const Shape& sh, bool backward, i
         case kAggregate: return launch_shape<IO, CPL, FEAT, kAggregate>(p, sh, backward, stream);
         case kExact: return launch_shape<IO, CPL, FEAT, kExact>(p, sh, backward, stream);
         case kGrouped: return launch_shape<IO, CPL, FEAT, kGrouped>(p, sh, backward, stream);
+        case kOwnGates: return launch_shape<IO, CPL, FEAT, kOwnGates>(p, sh, backward, stream);
         case kRecompute: return launch_shape<IO, CPL, FEAT, kRecompute>(p, sh, backward, stream);
         case kPaired:
             if constexpr (CPL == 8 && IO::ES == 2) return launch_shape<IO, CPL, FEAT, kPaired>(p, sh, backward, stream);

@@ -87,6 +87,7 @@ enum Mode {
                      // head (lanes 0-7 of a 16-lane row hold the first, 8-15 the second)
     kRecompute = 5,  // the jagged window's backward without saved block carriers: each step
                      // recomputes the carrier of the block before it from that block's x, b, a
+    kOwnGates = 6,   // kGrouped's forward with groups of one head: nothing is shared
 };
 
 // Sums the per-head float32 shares of db and dc that a kGrouped backward left

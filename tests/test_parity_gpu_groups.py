@@ -115,6 +115,17 @@ def test_group_of_one_matches_the_plain_calls(swr):
             assert torch.equal(p_, q_), name
 
 
+@pytest.mark.parametrize("D,block", [(16, 16), (32, 128), (64, 64), (128, 32)])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("logits", [False, True])
+def test_groups_of_one(swr, D, block, dtype, logits):
+    # a gate a head in the gates' own layout: nothing is shared, a forward of its own
+    prob = W.random_problem(24 + D, 2, 500, 4, D, block, dtype, logits=logits)
+    feat = dict(sigmoid_decay=True, sigmoid_pregate=True) if logits else {}
+    y, grads = _run(swr, prob, 1, residual=True, gate_layout="bgtd", **feat)
+    _check(prob, 1, y, grads, residual=True, what=f"groups of one {D} l{block} {dtype}", **feat)
+
+
 @pytest.mark.parametrize("D", [64, 128])
 def test_shared_gates_deterministic(swr, D):
     prob = W.random_problem(23, 2, 1500, 8, D, 128, "bf16")
