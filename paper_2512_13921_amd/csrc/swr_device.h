@@ -96,12 +96,16 @@ constexpr int kFwdStore = SWR_FWD_STORE_POLICY;
 constexpr int kBwdLoad = SWR_BWD_LOAD_POLICY;
 constexpr int kBwdStore = SWR_BWD_STORE_POLICY;
 
-// The streaming hint for rows of whole cache lines only: a row of fewer bytes
-// (heads of 16 channels, bf16 heads of 32, taken one at a time) shares its
+// The streaming hint for kernels whose rows are whole cache lines: a row of fewer
+// bytes (heads of 16 channels, bf16 heads of 32, taken one at a time) shares its
 // lines with other heads' or tokens' rows, which the hint drops before those
 // are read, or writes out in parts (bf16, 8 x 15 heads, D 16, T 69905: uniform
 // forward 665 -> 378 us, a decay per channel 965 -> 555, heads stored head by
-// head 539 -> 422; D 32, T 34952, uniform 367 -> 270).
+// head 539 -> 422; D 32, T 34952, uniform 367 -> 270).  It goes by the kernel's
+// width: rows of 48, 80, 96 or 112 channels, in kernels of 64 or 128, keep the
+// hint although they share lines too and run 1.02 to 1.27 times as long with it
+// (B8 T16384 H16 l64, bf16 D 48 219 us against 188, D 80 346 against 306, D 112
+// 418 against 392, float32 D 80 743 against 587; D 128 380 against 403).
 template <class IO, int CPL>
 struct Stream {
     static constexpr bool narrow = CPL * SB * IO::ES < 128;
