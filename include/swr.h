@@ -202,10 +202,10 @@ int swr_abi_version(void);
  * between workgroups in a fixed pattern, so that repeated calls give the same
  * bits): it reads every input once.  The backward does the same, from each
  * sequence's end, for heads of up to 64 channels (one decay per head).  With
- * one decay per head, problems of few bytes or few sequences, where that chain
- * and not the bytes would set the time, keep the three stages, and sequences
- * of up to 128 tokens run as a single run in either direction (the choice
- * depends on the problem's sizes alone).  A
+ * one decay per head, problems of few bytes whose chains are long or many,
+ * where these and not the bytes would set the time, keep the three stages, and
+ * sequences of up to 128 tokens run as a single run in either direction (the
+ * choice depends on the problem's sizes, strides and alignment alone).  A
  * chunk waits only for chunks that are already running, and gives up after
  * 65536 polls (never expected): it then adds one to the workspace's second
  * 32-bit integer and continues from NaN, so that every output depending on
