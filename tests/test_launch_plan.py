@@ -1,6 +1,7 @@
-"""Launch plans of the backward sweeps (CPU only): every run length is a
-multiple of the sweep's step that covers the sequence, and a grid of a few
-rounds of resident workgroups never starts another round."""
+"""Launch plans (CPU only): every run length is a multiple of the sweep's step
+that covers the sequence, a grid of a few rounds of resident workgroups never
+starts another round, one plan of each kind is pinned by its numbers, and
+packed heads stay within their bounds."""
 import pytest
 
 import paper_2512_13921_amd as swr
@@ -100,3 +101,22 @@ def test_odd_counts_with_sigmoids(D, block, sigmoid, packed):
 def test_odd_counts_in_the_forward_of_long_blocks(T, packed):
     i = swr.swr_launch_info(swr.make_problem(2, T, 3, 16, 128, swr.SWR_DTYPE_BF16, (T * 48, 48, 16), (T * 3, 3, 1)))
     assert i["fwd_workgroups"] // -(-T // i["fwd_run_len"]) == (2 if packed else 6)
+
+
+@pytest.mark.parametrize("B,T,H,D,block,dtype,per_channel,sigmoid,run,work", [
+    (8, 16384, 16, 128, 128, "bf16", False, False, 8192, 256),   # 8 waves: one round of 256
+    (3, 20000, 7, 64, 128, "bf16", False, False, 1792, 252),     # ... never just past one
+    (8, 4096, 16, 128, 64, "bf16", False, False, 512, 1024),     # 4 waves: runs of 512, whole rounds of 512
+    (1, 16384, 4, 64, 64, "bf16", False, False, 128, 512),       # too short for these: one round
+    (2, 8192, 33, 64, 64, "f32", False, False, 128, 4224),       # float32 lanes of 4: a grid of at most 8192
+    (2, 8192, 33, 64, 64, "bf16", False, True, 128, 4224),       # and bf16 with the sigmoids
+    (2, 8192, 33, 64, 64, "bf16", False, False, 576, 990),       # ... without: about 512, whole rounds
+    (4, 8192, 16, 32, 64, "bf16", True, False, 64, 8192),        # a decay per channel, 2 channels a lane
+    (1, 16384, 128, 16, 16, "bf16", False, False, 384, 1376),    # packed heads: runs of about 256
+])
+def test_pinned_backward_plans(B, T, H, D, block, dtype, per_channel, sigmoid, run, work):
+    xs = (T * H * D, H * D, D)
+    p = swr.make_problem(B, T, H, D, block, swr.SWR_DTYPE_BF16 if dtype == "bf16" else swr.SWR_DTYPE_F32, xs,
+                         xs if per_channel else (T * H, H, 1), per_channel=per_channel, sigmoid_decay=sigmoid)
+    i = swr.swr_launch_info(p)
+    assert (i["bwd_run_len"], i["bwd_workgroups"]) == (run, work)

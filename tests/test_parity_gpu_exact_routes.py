@@ -83,6 +83,51 @@ def test_exact_schedules(B, T, H, D, block, dtype, per_channel, states):
         assert_close(to_host(got), ref, dtype, name)
 
 
+FORMS = [
+    # (B, T, H, D, block, dtype, per_channel)
+    (2, 100, 6, 64, 64, "bf16", False),      # a single run
+    (1, 128, 3, 128, 128, "f32", True),      # ... of 64-channel halves
+    (2, 77, 8, 16, 16, "bf16", False),       # ... of packed heads (stored heads first: one at a time)
+    (1, 4999, 6, 64, 16, "bf16", False),     # three stages of pairs
+    (2, 1500, 5, 128, 128, "bf16", False),   # one pass
+    (1, 3000, 3, 32, 32, "bf16", True),      # one pass, three stages back
+]
+
+
+@pytest.mark.parametrize("B,T,H,D,block,dtype,per_channel", FORMS)
+@pytest.mark.parametrize("form", ["logits", "heads first", "long rows"])
+def test_exact_schedules_in_other_forms(B, T, H, D, block, dtype, per_channel, form):
+    import paper_2512_13921_amd as swr
+    logits = form == "logits"
+    prob = W.random_problem(T + D + 1, B, T, H, D, block, dtype, "sigmoid", 3.0, per_channel=per_channel, logits=logits)
+    feat = dict(sigmoid_decay=logits, sigmoid_pregate=logits)
+
+    def dev(n):
+        t = to_device(getattr(prob, n), dtype)
+        if form == "heads first":
+            return t.transpose(1, 2).contiguous().transpose(1, 2)
+        if form == "long rows":
+            w = t.stride(1)
+            return torch.empty_strided(t.shape, (T * (w + 64), w + 64) + t.stride()[2:], dtype=t.dtype,
+                                       device="cuda").copy_(t)
+        return t
+
+    x, a, b, c, dy = (dev(n) for n in ("x", "a", "b", "c", "dy"))
+    rng = np.random.default_rng(T)
+    h0, dhl = (rng.standard_normal((B, H, D)).astype(np.float32) for _ in range(2))
+    h0d, dhld = torch.from_numpy(h0).cuda(), torch.from_numpy(dhl).cuda()
+    y, v, hl = swr.swr_exact_forward(x, a, b, c, block, h0=h0d, residual=True, save_carriers=True, want_h_last=True,
+                                     **feat)
+    grads = swr.swr_exact_backward(x, a, b, c, dy, v, block, h0=h0d, dh_last=dhld, residual=True, want_dh0=True, **feat)
+    torch.cuda.synchronize()
+    ref_y, ref_hl = oracle.exact_forward(prob.x, prob.a, prob.b, prob.c, h0, residual=True, **feat)
+    refs = oracle.exact_backward(prob.x, prob.a, prob.b, prob.c, prob.dy, h0, dhl, residual=True, **feat)
+    assert_close(to_host(y), ref_y, dtype, "y")
+    assert_close(to_host(hl), ref_hl, dtype, "h_last")
+    for name, got, ref in zip(("dx", "da", "db", "dc", "dh0"), grads, refs):
+        assert_close(to_host(got), ref, dtype, name)
+
+
 def test_time_out_path_of_the_chains(monkeypatch):
     # Both one-pass schedules (paired-head forward, backward) at a size that
     # chains, with the poll limit forced to 0 from the host: the kernels end,

@@ -128,3 +128,41 @@ def test_decays_of_far_apart_heads(swr, H, D, log2_stride):
     for name, got, ref in zip(("dx", "da", "db", "dc"), grads, oracle.exact_backward(prob.x, prob.a, prob.b, prob.c,
                                                                                     prob.dy)):
         assert_close(to_host(got), ref, "bf16", name)
+
+
+def _form(t, form):
+    """t's values in another storage that the calls accept: heads-first, rows
+    longer than their heads, or aligned for one head's lanes but not the packed
+    ones' (heads of D channels: D / 16 elements off)."""
+    if form == "heads first":
+        return _strided_like(t, (t.stride(0), 1, t.shape[1]) if t.dim() == 3 else t.stride())
+    if form == "long rows":
+        w = t.stride(1)
+        return _strided_like(t, (t.shape[1] * (w + 64), w + 64) + t.stride()[2:])
+    buf = torch.empty(t.numel() + 8, dtype=t.dtype, device="cuda")
+    r = buf[t.shape[3] // 16 if t.dim() == 4 else 1:][:t.numel()].view(t.shape)
+    return r.copy_(t)
+
+
+@pytest.mark.parametrize("B,T,H,D,block", [(2, 2500, 7, 16, 16), (3, 3700, 3, 32, 32), (1, 11000, 7, 16, 128)])
+@pytest.mark.parametrize("form", ["heads first", "long rows", "misaligned"])
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_odd_head_counts_in_other_storage(swr, B, T, H, D, block, form, dtype):
+    # (heads first: of a and da alone; misaligned: the heads run one by one)
+    prob = W.random_problem(186 + T + H, B, T, H, D, block, dtype, "sigmoid", 3.0)
+    x, a, b, c, dy = (_form(to_device(getattr(prob, n), dtype), form) for n in ("x", "a", "b", "c", "dy"))
+    y, v = swr.swr_forward(x, a, b, c, block, save_carriers=True)
+    for carriers in (v, None):
+        grads = swr.swr_backward(x, a, b, c, dy, carriers, block)
+        torch.cuda.synchronize()
+        assert grads[1].stride() == a.stride()
+        check_full(prob, y, grads, what=f"odd {form} {dtype}")
+    ye, ve, hl = swr.swr_exact_forward(x, a, b, c, block, save_carriers=True, want_h_last=True)
+    grads = swr.swr_exact_backward(x, a, b, c, dy, ve, block)
+    torch.cuda.synchronize()
+    ref_y, ref_hl = oracle.exact_forward(prob.x, prob.a, prob.b, prob.c)
+    assert_close(to_host(ye), ref_y, dtype, "y")
+    assert_close(to_host(hl), ref_hl, dtype, "h_last")
+    for name, got, ref in zip(("dx", "da", "db", "dc"), grads, oracle.exact_backward(prob.x, prob.a, prob.b, prob.c,
+                                                                                    prob.dy)):
+        assert_close(to_host(got), ref, dtype, name)
