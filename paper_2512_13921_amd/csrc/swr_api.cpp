@@ -661,6 +661,9 @@ bool use_chain_bwd(const swr_problem_t* p, const Resolved& r) {
 //     but 7 of 1024 11.6 / 13.3, 127 of 384 16.8 / 17.6; heads of 16, 64 of 512
 //     11.7 / 10.5; but 8 of 1024 9.5 / 11.4; in float32 chains of 64 chunks on:
 //     heads of 32, 4 of 32768 48 / 35
+//   at l 128 the stages' runs are 128 tokens at least, half as many workgroups:
+//     pairs, 16 of 512 13.0 / 14.5, heads of 64, 7 of 2048 14.3 / 16.0; their lines
+//     lie at longer chains
 //   backward, D 64: 4 of 131072 215 / 160, 8 of 8192 34 / 28, 8 of 32768 74 /
 //     77, 16 of 131072 523 / 468, 32 of 131072 928 / 1047; chains of up to 32
 //     chunks are within 10%.
@@ -669,12 +672,15 @@ bool prefer_stages(const swr_problem_t* p, const Resolved& r, bool backward, boo
     const int64_t row = p->B * p->H * p->D * r.es, total = row * p->T;
     if (backward)
         return nch > 32 && (total <= (int64_t)12 << 20 || row <= 512 || (row <= 2048 && nch >= 512));
+    const bool l128 = p->block == 128, d64 = p->D == 64;
     if (pair)
-        return row <= 1024 || (row <= 2048 && total <= (int64_t)32 << 20) ||
-               (row <= 4096 && total <= (int64_t)16 << 20) || (row <= 8192 && p->T <= 512);
-    if (p->D == 128) return r.es == 2 && nch >= 48 && row <= 1536;
-    const bool d64 = p->D == 64;
-    const bool chained = r.es == 4 ? nch >= 64 : nch >= (d64 ? 11 : 32) || p->B * p->H * nch >= (d64 ? 480 : 256);
+        return (!l128 || nch >= 11) &&
+               (row <= 1024 || (row <= 2048 && total <= (int64_t)32 << 20) ||
+                (row <= 4096 && total <= (int64_t)16 << 20) || (row <= 8192 && p->T <= 512));
+    if (p->D == 128)
+        return r.es == 2 && nch >= (l128 ? 64 : 48) && (row <= 1024 || (row <= 1536 && total <= (int64_t)32 << 20));
+    const bool chained = r.es == 4 ? nch >= 64
+                                   : nch >= (d64 && !l128 ? 11 : 32) || p->B * p->H * nch >= (d64 || l128 ? 480 : 256);
     return chained && (total <= (int64_t)24 << 20 || row <= 1024);
 }
 

@@ -21,7 +21,12 @@ CASES = [
     (1, 100, 5, 32, 32, "f32", True),
     (2, 128, 8, 16, 64, "bf16", False),      # ... of packed heads
     (1, 128, 2, 128, 64, "bf16", True),      # ... of 64-channel halves
-    (1, 129, 2, 64, 128, "bf16", False),     # three-stage forward, one-pass backward
+    (1, 64, 3, 128, 32, "f32", False),       # float32 heads of 128: a single run forward up to 64 tokens
+    (1, 65, 3, 128, 32, "f32", False),       # and a chain of one chunk from there on
+    (1, 129, 2, 64, 128, "bf16", False),     # pairs at l = 128: one pass up to 10 chunks
+    (1, 129, 2, 64, 32, "bf16", False),      # three-stage forward, one-pass backward
+    (1, 1280, 2, 64, 128, "bf16", False),    # 10 chunks
+    (1, 1281, 2, 64, 128, "bf16", False),    # 11 chunks: three stages
     (1, 4096, 2, 64, 64, "bf16", False),     # the backward's last chain of 32 chunks
     (1, 4097, 2, 64, 64, "bf16", False),     # and its first 33 chunks in three stages
     (2, 8192, 3, 64, 128, "f32", False),     # float32: 64 chunks, 12.6 MB (backward one-pass)
