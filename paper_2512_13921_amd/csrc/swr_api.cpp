@@ -688,10 +688,13 @@ bool prefer_stages(const swr_problem_t* p, const Resolved& r, bool backward, boo
 // as one run: no stage I or II, the sweep starts from h0 (dh_last) and stores
 // h_last (dh0) itself; one launch instead of two or three.  bf16, 15 sequences
 // of 128 tokens, D 64: forward 10.8 -> 7.5 us, backward 13.2 -> 10.4; of 256
-// tokens the backward's two steps would take 15.7 us against 14.6.
+// tokens the backward's two steps would take 15.7 us against 14.6.  The forward
+// of float32 heads of 128 gains up to 64 tokens only, one of its steps (32
+// sequences of 64 tokens 9.3 -> 6.9 us, of 128 12.2 against the chain's 9.7).
 constexpr int64_t kOneRunTokens = 128;
-bool one_run(const swr_problem_t* p, const Resolved& r) {
-    return !r.empty && p->run_len == 0 && p->T <= kOneRunTokens;
+bool one_run(const swr_problem_t* p, const Resolved& r, bool backward) {
+    const int64_t most = !backward && p->D == 128 && r.es == 4 && !r.pc ? 64 : kOneRunTokens;
+    return !r.empty && p->run_len == 0 && p->T <= most;
 }
 
 // The one-pass forward of bf16 heads of 64 channels taken two at a time
@@ -787,7 +790,7 @@ int swr::exact_forward_impl(const swr_problem_t* p, const void* x, const void* a
                 resolve_for(p, &rp, Use::kForward, {x, b, c, (const void*)y}) == SWR_OK && rp.pair &&
                 (!scratch || chain_pair_floats(p) * 4 <= scratch_bytes);
     bool chain = !pair && use_chain(p, r) && (!scratch || chain_ws(p, r).floats * 4 <= scratch_bytes);
-    const bool single = one_run(p, r);   // (needs no array, but is refused where nothing fits)
+    const bool single = one_run(p, r, false);   // (needs no array, but is refused where nothing fits)
     const bool fits = pair || chain || stages_fit;
     if (single || (!r.pc && stages_fit && prefer_stages(p, r, false, pair))) pair = chain = false;
     const int64_t wfloats = pair ? chain_pair_floats(p) : chain ? chain_ws(p, r).floats : w.floats;
@@ -943,7 +946,7 @@ int swr_exact_backward(const swr_problem_t* p, const void* x, const void* a, con
             if (overlap(outs[i], outs[j])) return SWR_ERR_ALIAS;
     }
 
-    const bool single = one_run(p, r);
+    const bool single = one_run(p, r, true);
     if (!single && use_chain_bwd(p, r) && !prefer_stages(p, r, true, false)) {   // one pass: chunks from the sequences' ends, chained by a look-back
         const ChainWs cw = chain_ws(p, r);
         float* f = (float*)workspace;
