@@ -1145,11 +1145,12 @@ int uni_resolve(const swr_problem_t* p, UniPlan* u, bool backward) {
     // channels: 117 VGPRs against 156 and 236), one round.  The forward: two,
     // and runs of 2048 tokens once those make several rounds (measured on
     // MI355X against 512 workgroups: B8 T16384 H16 d128 455 -> 438 us, B1
-    // T131072 H32 d64 466 -> 449, B16 T8192 H32 d64 426 -> 423).
+    // T131072 H32 d64 466 -> 449, B16 T8192 H32 d64 426 -> 423).  The forward's
+    // halo solves its block as a step does, and counts whole.
     if (p->run_len > 0)
         u->run_len = p->run_len;
     else
-        u->run_len = plan_run_len(p->T, groups, p->block, p->block,
+        u->run_len = plan_run_len(p->T, groups, p->block, backward ? p->block : 2 * p->block,
                                   backward ? Sweep{u->cpl == 1 ? 512 : 256, 0} : Sweep{512, 2048});
     u->nruns = (p->T + u->run_len - 1) / u->run_len;
     if (u->nruns > kMaxWorkgroups / groups) return SWR_ERR_UNSUPPORTED;
